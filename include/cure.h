@@ -205,6 +205,8 @@ cure_status cure_margins_noalloc(const void* logits, int32_t dtype, int32_t batc
  * Alignment (else CURE_ERR_INVALID_ARG): workspace 16 bytes; on the bf16
  * matrix-core path (bf16 inputs, d 64 or 128, scale > 0, no FORCE_VALU) also
  * q, k, v 16 bytes and o 8 bytes (bf16 out) or 16 bytes (fp32 out).
+ * fp32 inputs run on the fp32 matrix instructions when q, k, v and o have that
+ * alignment, and on the vector-ALU kernel otherwise.
  */
 size_t cure_tree_attn_workspace_size(int32_t batch, int32_t hq, int32_t hkv, int32_t d,
                                      int32_t n_max, const int32_t* host_ctx_len,

@@ -10,7 +10,7 @@
 // of every tree node, packed node-major. Only tiles that reach the tree rows
 // at the tail of the sequence apply the ancestor bitmask.
 //
-// Three kernels compute a split:
+// Four kernels compute a split:
 //  * tree_attn_m16: bf16, scale > 0, head dim 128 (any row count, in
 //    balanced row blocks of up to 256 rows) or 64 (up to 128 rows). Scores
 //    are formed transposed, S^T = K Q^T, and the output as O^T = V^T P^T with
@@ -19,8 +19,10 @@
 //    exactly the token order the score MFMA leaves P in registers.
 //  * tree_attn_mfma: the same scheme with 32x32x16 MFMAs and 32 rows per
 //    wave, for head dim 64 beyond 128 rows.
-//  * tree_attn_valu: fp32 or bf16, any supported shape and scale; plain vector
-//    ALU code.
+//  * tree_attn_f32: fp32 on the fp32 matrix instructions, the same scheme with
+//    the rows or the tokens of a block dealt over four waves.
+//  * tree_attn_valu: fp32 or bf16, any supported shape, scale and alignment;
+//    plain vector ALU code.
 // A split writes normalised partial O and its log-sum-exp; attn_merge combines
 // the splits of each row (skipped when a sequence has a single split, in which
 // case the split kernel writes the final output itself).
@@ -41,6 +43,12 @@ constexpr int kTile = 64;            // tokens per K/V tile
 constexpr int kStages = 2;           // K/V tile buffers in the MFMA kernel's LDS ring
 constexpr int kMaxGridY = 65535;     // largest grid y (the split index)
 constexpr int kMinTps = 256;         // tokens per split, at least
+// The fp32 matrix kernel is bound by arithmetic (3.5 us per 64 tokens and wave
+// at head dim 128), so shorter splits pay for their merge earlier: a batch of
+// 4 at 32 nodes takes 39.8 us per call at 64, 128 and 192 tokens (the plan's
+// own split is 192), 46.9 at 256. A block of 16 rows spreads its tokens over
+// four waves and keeps kMinTps.
+constexpr int kMinTpsF32 = 128;
 constexpr int kAncWords = CURE_MAX_TREE_NODES / 64;
 
 struct Args {
@@ -1381,6 +1389,304 @@ void tree_attn_rg(Args a) {
 }
 
 // ---------------------------------------------------------------------------
+// fp32 split kernel on the matrix cores (v_mfma_f32_16x16x4_f32, fp32 products
+// and sums: the same precision as the vector-ALU kernel).
+//
+// Bound by the fp32 matrix rate (256 flop per clock and CU; a large fp32 GEMM
+// reaches 137 TFLOP/s on this card), 16 flop of it per K/V byte and query row,
+// so K/V traffic only matters for a few rows per kv-head. A workgroup is four
+// waves, each owning 16 query rows and 1 / WT of every tile's tokens: WT = 1
+// for 64 rows per block, and the waves share a block of 32 or 16 rows by
+// tokens (WT = 2, 4) when a kv-head has no more, so no wave idles; the token
+// shares are combined through LDS at the end. Measured per call against the
+// vector-ALU kernel, which it replaces for aligned operands (its LDS broadcast
+// of every query element per multiply bound it to 11 TFLOP/s): 4 sequences of
+// 850 - 1780 tokens, 32 nodes, 32/8 heads of 128: 257 -> 39.8 us, 70 TFLOP/s
+// with the merge; one sequence of 128 tokens, 12 nodes, 4 heads of 64: 29.2 ->
+// 7.7 us in the kernel.
+//
+// Lane l = 16 g + c owns query row c of its wave's 16.
+//   S^T = K Q^T, 16 tokens at a time: MFMA i of column group j (16 columns)
+//     takes k index g for column 16 j + 4 g + i, so that one 16-byte read of K
+//     (row c, columns 16 j + 4 g .. +3) feeds four MFMAs
+//     D register r = score of token 4 g + r for row c
+//   O^T += V^T P^T: MFMA r takes k index g for token 4 g + r, the probability
+//     the lane already holds in register r; output row c' of block 4 h + i
+//     stands for column 64 h + 4 c' + i, so that one 16-byte read of V (row
+//     4 g + r, columns 64 h + 4 c .. +3) feeds four MFMAs
+//     D register r of block 4 h + i = O column 64 h + 16 g + 4 r + i of row c
+// LDS rows are XOR-swizzled by 16-byte chunk: the K reads (16 rows, one chunk
+// column) and the V reads (one row, 16 chunks) both cover all banks evenly.
+// Hidden and out-of-range scores are replaced, not added to: an infinite or NaN
+// K row that a node does not see leaves its result alone.
+template <int D, int WT>
+struct F32Geo {
+  static constexpr int kTok = WT == 4 ? 64 : 32;         // tokens per K/V tile
+  static constexpr int kTB = kTok / 16 / WT;             // 16-token blocks per wave and tile
+  static constexpr int kRows = 64 / WT;                  // query rows per workgroup
+  static constexpr int kRowBytes = D * 4;
+  static constexpr int kTileBytes = kTok * kRowBytes;
+  static constexpr int kDmaPerWave = kTileBytes / 1024 / 4;
+  static constexpr int kWgsPerCu = kTileBytes > 16384 ? 1 : 2;   // LDS: two tiles of K and of V
+  static CURE_DEV int offset(int row, int chunk) { return row * kRowBytes + ((chunk ^ (row & 15)) << 4); }
+};
+
+template <int D, int WT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((F32Geo<D, WT>::kWgsPerCu))))
+void tree_attn_f32(Args a) {
+  using G = F32Geo<D, WT>;
+  constexpr int kTB = G::kTB;
+  constexpr int kKGroups = D / 16;                 // 16-column groups of Q K^T
+  constexpr int kDBlk = D / 16;                    // output blocks of 16 columns
+  constexpr int kH = D / 64;
+
+  __shared__ int s_parent[CURE_MAX_TREE_NODES];
+  __shared__ unsigned long long s_anc[CURE_MAX_TREE_NODES][kAncWords];
+  __shared__ int s_bad;
+  __shared__ __attribute__((aligned(1024))) unsigned char s_kv[2][2][G::kTileBytes];  // [buffer][K, V]
+
+  const int b = blockIdx.z;
+  const int hk = blockIdx.x % a.hkv;
+  const int rb = blockIdx.x / a.hkv;
+  const int s = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = lane & 15, g = lane >> 4;
+  const int wt = wave % WT, wr = wave / WT;        // this wave's share of the tokens and its rows
+
+  // Query loads (they need only the launch shape) and the parent entry go out
+  // with the loads of the sequence's sizes.
+  const int R = rb * G::kRows + wr * 16 + c;
+  const bool r_in = R < a.n_max * a.group;
+  f32x4 qreg[kKGroups];
+  {
+    const int qn = r_in ? R / a.group : 0;
+    const int qh = hk * a.group + (r_in ? R % a.group : 0);
+    const float* qrow = reinterpret_cast<const float*>(a.q) + (((int64_t)b * a.n_max + qn) * a.hq + qh) * D;
+#pragma unroll
+    for (int j = 0; j < kKGroups; ++j)
+      qreg[j] = r_in ? *reinterpret_cast<const f32x4*>(qrow + 16 * j + 4 * g) : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const int my_parent = tid < a.n_max ? a.parent[(int64_t)b * a.n_max + tid] : -1;
+
+  const int n_raw = a.n_nodes[b];
+  const int L = a.ctx_len[b];
+  const int64_t off = a.kv_off[b];
+  asm volatile("" : : "s"(n_raw), "s"(L), "s"(off));
+  const int N = min(n_raw, a.n_max);
+  const int T = L + N;
+  const int S = split_count(T, N, a.tps, a.max_splits);
+  const int rows = N * a.group;
+  if (S == 0) {                         // no nodes: nothing to compute; the empty tree is valid
+    report_tree(a, b, true, s == 0 && hk == 0 && rb == 0);
+    return;
+  }
+  if (s >= S || rb * G::kRows >= rows) return;
+
+  const int begin = s * a.tps;
+  const int end = (s == S - 1) ? T : begin + a.tps;
+
+  // The tile DMA of the bf16 kernels: per lane and 1 KB block, the byte offset
+  // of its source chunk for tile start 0; rows past the sequence read as zeros.
+  const uint32_t tok_bytes = (uint32_t)(a.hkv * G::kRowBytes);
+  const uint32_t seq_bytes = (uint32_t)T * tok_bytes;
+  uint32_t src_off[G::kDmaPerWave];
+#pragma unroll
+  for (int j = 0; j < G::kDmaPerWave; ++j) {
+    const int byte = (wave * G::kDmaPerWave + j) * 1024 + lane * 16;
+    const int row = byte / G::kRowBytes;
+    const int pchunk = (byte % G::kRowBytes) >> 4;
+    src_off[j] = (uint32_t)row * tok_bytes + (uint32_t)(hk * G::kRowBytes + ((pchunk ^ (row & 15)) << 4));
+  }
+  const i32x4 rk4 = raw_rsrc(reinterpret_cast<const float*>(a.k) + off * a.hkv * D, seq_bytes);
+  const i32x4 rv4 = raw_rsrc(reinterpret_cast<const float*>(a.v) + off * a.hkv * D, seq_bytes);
+  auto dma_tile = [&](int buf, int t0) {
+    const bool live = t0 < end;
+#pragma unroll
+    for (int j = 0; j < G::kDmaPerWave; ++j) {
+      const uint32_t voff = live ? src_off[j] + (uint32_t)t0 * tok_bytes : kOobOffset;
+      const int blk = (wave * G::kDmaPerWave + j) * 1024;
+      dma16(lds_addr(&s_kv[buf][0][blk]), voff, rk4);
+      dma16(lds_addr(&s_kv[buf][1][blk]), voff, rv4);
+    }
+  };
+  dma_tile(0, begin);
+
+  const bool row_ok = R < rows;
+  const int n = row_ok ? R / a.group : 0;
+  const int head = hk * a.group + (row_ok ? R % a.group : 0);
+  const bool wave_active = rb * G::kRows + wr * 16 < rows;
+
+  int k_off[kKGroups];                             // K: row 16 (kTB wt + tb) + c, chunk 4 j + g
+#pragma unroll
+  for (int j = 0; j < kKGroups; ++j) k_off[j] = G::offset(kTB * wt * 16 + c, 4 * j + g);
+  int v_off[4];                                    // V: row 16 (kTB wt + tb) + 4 g + r, chunk 16 h + c
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v_off[r] = G::offset(kTB * wt * 16 + 4 * g + r, c);
+
+  // Only a split that reaches the tree's own rows needs the ancestor masks.
+  if (end > L) {
+    const bool ok = build_tree_loaded(N, my_parent, s_parent, s_anc, &s_bad);
+    report_tree(a, b, ok, s == S - 1 && hk == 0 && rb == 0);
+    if (!ok) {
+      __builtin_amdgcn_s_waitcnt(0);               // no DMA may land after the workgroup ends
+      return;
+    }
+  }
+
+  f32x4 oacc[kDBlk];
+#pragma unroll
+  for (int i = 0; i < kDBlk; ++i) oacc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run = -INFINITY, l_run = 0.f;            // l_run: this lane's share of the row sum
+  const float cs = a.scale_log2;
+
+  __builtin_amdgcn_s_waitcnt(0);
+  if (!row_ok) {
+#pragma unroll
+    for (int j = 0; j < kKGroups; ++j) qreg[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int t0 = begin, buf = 0; t0 < end; t0 += G::kTok, buf ^= 1) {
+    __builtin_amdgcn_s_waitcnt(0);                 // this wave's DMA into `buf` has landed
+    __syncthreads();                               // everyone's has; the other buffer is free
+    dma_tile(buf ^ 1, t0 + G::kTok);
+    if (!wave_active) continue;
+    const unsigned char* kt = s_kv[buf][0];
+    const unsigned char* vt = s_kv[buf][1];
+
+    f32x4 sacc[kTB];
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb) sacc[tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < kKGroups; ++j) {
+      f32x4 kf[kTB];
+#pragma unroll
+      for (int tb = 0; tb < kTB; ++tb)
+        kf[tb] = *reinterpret_cast<const f32x4*>(kt + tb * 16 * G::kRowBytes + k_off[j]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int tb = 0; tb < kTB; ++tb)
+          sacc[tb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[tb][i], qreg[j][i], sacc[tb], 0, 0, 0);
+    }
+    // Scores in the log2 domain; hidden ones become -inf.
+    float x[kTB][4];
+    const bool tail = t0 + G::kTok > L;
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x[tb][r] = sacc[tb][r] * cs;
+    if (tail) {
+#pragma unroll
+      for (int tb = 0; tb < kTB; ++tb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int tok = t0 + (kTB * wt + tb) * 16 + 4 * g + r;
+          x[tb][r] = mask_bias(tok, L, end, n, s_anc) == 0.f ? x[tb][r] : -INFINITY;
+        }
+    }
+    float mt = -INFINITY;
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mt = fmaxf(mt, x[tb][r]);
+    mt = max_halves(fmaxf(mt, partner<16>(mt)));   // the row's tokens sit in lanes c + 16 k
+    const float m_new = fmaxf(m_run, mt);
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
+    if (__ballot(m_new > m_run)) {                 // a maximum rose: rescale (factor 1 for the others)
+      const float alpha = fast_exp2(m_run - m_use);
+      l_run *= alpha;
+#pragma unroll
+      for (int i = 0; i < kDBlk; ++i) oacc[i] *= alpha;
+    }
+    m_run = m_new;
+    float p[kTB][4], ps = 0.f;
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        p[tb][r] = fast_exp2(x[tb][r] - m_use);
+        ps += p[tb][r];
+      }
+    l_run += ps;
+#pragma unroll
+    for (int tb = 0; tb < kTB; ++tb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int h = 0; h < kH; ++h) {
+          const f32x4 vf = *reinterpret_cast<const f32x4*>(vt + tb * 16 * G::kRowBytes + h * 256 + v_off[r]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            oacc[4 * h + i] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i], p[tb][r], oacc[4 * h + i], 0, 0, 0);
+        }
+  }
+
+  __builtin_amdgcn_s_waitcnt(0);                   // the trailing out-of-range DMA lands before LDS is reused
+  float l_tot = l_run + partner<16>(l_run);
+  l_tot = sum_halves(l_tot);
+  if (WT > 1) {
+    // The other token shares of these rows: [wr][wt - 1] records of D + 2
+    // floats per row in the tile buffers, which every wave is done with.
+    __syncthreads();
+    float* s_o = reinterpret_cast<float*>(&s_kv[0][0][0]);
+    constexpr int kRec = 64 * (4 * kDBlk + 2);     // floats per wave
+    static_assert(4 * kRec * 4 <= (int)sizeof(s_kv), "the token shares fit the tile buffers");
+    if (wt > 0) {
+      float* d = s_o + wave * kRec + lane;
+#pragma unroll
+      for (int i = 0; i < kDBlk; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) d[64 * (4 * i + r)] = oacc[i][r];
+      d[64 * 4 * kDBlk] = m_run;
+      d[64 * (4 * kDBlk + 1)] = l_tot;
+    }
+    __syncthreads();
+    if (wt > 0) return;
+#pragma unroll
+    for (int w = 1; w < WT; ++w) {
+      const float* d = s_o + (wave + w) * kRec + lane;
+      const float m2 = d[64 * 4 * kDBlk], l2 = d[64 * (4 * kDBlk + 1)];
+      const float m_new = fmaxf(m_run, m2);
+      const float m_use = m_new == -INFINITY ? 0.f : m_new;
+      const float a1 = fast_exp2(m_run - m_use), a2 = fast_exp2(m2 - m_use);
+      l_tot = l_tot * a1 + l2 * a2;
+#pragma unroll
+      for (int i = 0; i < kDBlk; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) oacc[i][r] = oacc[i][r] * a1 + d[64 * (4 * i + r)] * a2;
+      m_run = m_new;
+    }
+  }
+  if (!row_ok) return;
+  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  const float lse_nat = l_tot > 0.f ? (m_run + log2f(l_tot)) * kLn2 : -INFINITY;
+  const int64_t orow = ((int64_t)b * a.n_max + n) * a.hq + head;
+  const int64_t pi = S == 1 ? 0 : part_index(a, b, head, n, s);
+#pragma unroll
+  for (int h = 0; h < kH; ++h)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int d0 = 64 * h + 16 * g + 4 * r;
+      const float4 x = make_float4(oacc[4 * h][r] * inv, oacc[4 * h + 1][r] * inv,
+                                   oacc[4 * h + 2][r] * inv, oacc[4 * h + 3][r] * inv);
+      if (S > 1) {
+        *reinterpret_cast<float4*>(a.part_o + pi * D + d0) = x;
+      } else if (a.out_bf16) {
+        uint2 pk;
+        pk.x = pack_bf16x2(x.x, x.y);
+        pk.y = pack_bf16x2(x.z, x.w);
+        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.o) + orow * D + d0) = pk;
+      } else {
+        *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.o) + orow * D + d0) = x;
+      }
+    }
+  if (g == 0) {
+    if (S > 1) a.part_lse[pi] = lse_nat;
+    else if (a.lse) a.lse[orow] = lse_nat;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // LSE merge: one wave per output row (b, n, head).
 //
 // A split's partial row is D floats = D/4 lanes of float4, so one load
@@ -1506,8 +1812,10 @@ __global__ __launch_bounds__(256) void tree_status_ok(int32_t* status, int batch
 
 // ---------------------------------------------------------------------------
 // Host-side plan: tokens per split and the launch shape.
+enum class Path { kValu, kF32, kBf16 };   // kernel family: vector ALU, fp32 or bf16 matrix cores
+
 struct Plan {
-  bool mfma;
+  Path path;
   bool rows16;        // MFMA kernel with 16 query rows per wave
   bool rows48;        // MFMA kernel with three 16-row groups per wave (tree_attn_rg)
   int nw;             // waves per workgroup (MFMA kernel)
@@ -1544,9 +1852,10 @@ int mfma_wgs_per_cu(int d, int nw, bool rows16, bool rows48) {
 
 Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
                const int32_t* host_ctx_len, const int32_t* host_n_nodes, int32_t kv_split,
-               bool mfma) {
+               Path path) {
   Plan p{};
-  p.mfma = mfma;
+  p.path = path;
+  const bool mfma = path == Path::kBf16;
   const int group = hq / hkv;
   const int rows = n_max * group;
   // Head dim 128: the 16-row kernel, in balanced row blocks of at most 256
@@ -1576,6 +1885,11 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
     if (mfma) {
       p.nw = 8;
       p.rows_per_wg = 32 * p.nw;
+    } else if (path == Path::kF32) {
+      // Four waves of 16 rows each; with 32 or 16 rows or fewer the waves
+      // share the rows and split the tokens (F32Geo's WT = 2, 4).
+      p.nw = 4;
+      p.rows_per_wg = rows <= 16 ? 16 : rows <= 32 ? 32 : 64;
     } else {
       p.nw = kValuWaves;
       p.rows_per_wg = kValuRows;
@@ -1602,15 +1916,19 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
     }
     return c * hkv * p.row_blocks;
   };
-  const int64_t slots =
-      (int64_t)(mfma ? mfma_wgs_per_cu(d, p.nw, p.rows16, p.rows48) : 2) * device_cu_count();
-  // The shortest split (at least kMinTps tokens) whose workgroups are all
+  const int wgs_per_cu = mfma ? mfma_wgs_per_cu(d, p.nw, p.rows16, p.rows48)
+                         : path == Path::kF32 && d == 128 && p.rows_per_wg == 16
+                             ? F32Geo<128, 4>::kWgsPerCu
+                             : 2;
+  const int64_t slots = (int64_t)wgs_per_cu * device_cu_count();
+  const int min_tps = path == Path::kF32 && p.rows_per_wg > 16 ? kMinTpsF32 : kMinTps;
+  // The shortest split (at least min_tps tokens) whose workgroups are all
   // resident at once, so no workgroup waits for a second round. A batch with
   // more sequence x head pairs than that gets a single split per sequence.
   const auto shortest_resident_split = [&]() {
     const int64_t hi = round_tile(t_max);
     const int64_t lo = round_tile(std::max<int64_t>(
-        kMinTps, (t_sum * hkv * p.row_blocks + slots - 1) / std::max<int64_t>(1, slots)));
+        min_tps, (t_sum * hkv * p.row_blocks + slots - 1) / std::max<int64_t>(1, slots)));
     if (lo >= hi || workgroups(hi) > slots) return hi;
     // workgroups() falls as tps grows: bisect over multiples of the tile.
     int64_t a = lo / kTile, z = hi / kTile;         // workgroups(z * kTile) <= slots
@@ -1662,8 +1980,24 @@ size_t plan_workspace(const Plan& p, int32_t batch, int32_t hq, int32_t d, int32
   return align_up(parts * d * sizeof(float), 256) + align_up(parts * sizeof(float), 256);
 }
 
-bool use_mfma(int32_t dtype, int32_t d, uint32_t flags) {
-  return dtype == CURE_BF16 && (d == 64 || d == 128) && !(flags & CURE_ATTN_FORCE_VALU);
+// The kernel family of a call, from its types, sizes and alignment. Every
+// matrix-core kernel addresses a sequence's K/V rows with 32-bit byte offsets.
+//  * bf16: takes the row maximum on raw scores, so scale > 0; operands that are
+//    not 16-byte aligned are refused later on.
+//  * fp32: any finite scale; operands that are not 16-byte aligned (o: 8 bytes
+//    for a bf16 output) stay on the vector-ALU kernel, which takes them all.
+Path choose_path(int32_t dtype, int32_t out_dtype, int32_t d, int32_t hkv, float scale,
+                 uint32_t flags, int64_t t_max, const void* q, const void* k, const void* v,
+                 const void* o) {
+  const int64_t elem = dtype == CURE_BF16 ? 2 : 4;
+  if ((flags & CURE_ATTN_FORCE_VALU) || !std::isfinite(scale) ||
+      (t_max + kTile) * hkv * d * elem >= (int64_t(1) << 31))
+    return Path::kValu;
+  if (dtype == CURE_BF16) return scale > 0.f ? Path::kBf16 : Path::kValu;
+  const uintptr_t in = reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k) |
+                       reinterpret_cast<uintptr_t>(v);
+  const uintptr_t out = reinterpret_cast<uintptr_t>(o) % (out_dtype == CURE_BF16 ? 8 : 16);
+  return in % 16 == 0 && out == 0 ? Path::kF32 : Path::kValu;
 }
 
 }  // namespace
@@ -1679,10 +2013,13 @@ extern "C" size_t cure_tree_attn_workspace_size(int32_t batch, int32_t hq, int32
   if (batch <= 0 || hq <= 0 || hkv <= 0 || hq % hkv || n_max <= 0 || !host_ctx_len ||
       !host_n_nodes)
     return 0;
-  // The MFMA and VALU plans may differ in row blocking; report the larger need.
-  const Plan pm = make_plan(batch, hq, hkv, d, n_max, host_ctx_len, host_n_nodes, kv_split, true);
-  const Plan pv = make_plan(batch, hq, hkv, d, n_max, host_ctx_len, host_n_nodes, kv_split, false);
-  return std::max(plan_workspace(pm, batch, hq, d, n_max), plan_workspace(pv, batch, hq, d, n_max));
+  // The kernel families' plans may differ in row blocking; report the largest need.
+  size_t need = 0;
+  for (const Path path : {Path::kValu, Path::kF32, Path::kBf16}) {
+    const Plan p = make_plan(batch, hq, hkv, d, n_max, host_ctx_len, host_n_nodes, kv_split, path);
+    need = std::max(need, plan_workspace(p, batch, hq, d, n_max));
+  }
+  return need;
 }
 
 extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* v, void* o,
@@ -1716,16 +2053,12 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
   for (int b = 0; b < batch; ++b)
     if (host_ctx_len[b] < 0 || host_n_nodes[b] < 0 || host_n_nodes[b] > n_max)
       return CURE_ERR_INVALID_ARG;
-  // The MFMA kernel takes the row maximum on raw scores (valid for scale > 0)
-  // and addresses a sequence's K/V rows with 32-bit byte offsets.
-  bool mfma = use_mfma(dtype, d, flags) && scale > 0.f && std::isfinite(scale);
-  if (mfma) {
-    int64_t t_max = 0;
-    for (int b = 0; b < batch; ++b)
-      t_max = std::max<int64_t>(t_max, (int64_t)host_ctx_len[b] + host_n_nodes[b]);
-    if ((t_max + kTile) * hkv * d * 2 >= (int64_t(1) << 31)) mfma = false;
-  }
-  const Plan p = make_plan(batch, hq, hkv, d, n_max, host_ctx_len, host_n_nodes, kv_split, mfma);
+  int64_t t_max = 0;
+  for (int b = 0; b < batch; ++b)
+    t_max = std::max<int64_t>(t_max, (int64_t)host_ctx_len[b] + host_n_nodes[b]);
+  const Path path = choose_path(dtype, out_dtype, d, hkv, scale, flags, t_max, q, k, v, o);
+  const bool mfma = path == Path::kBf16;
+  const Plan p = make_plan(batch, hq, hkv, d, n_max, host_ctx_len, host_n_nodes, kv_split, path);
   if (p.max_splits == 0) {              // no sequence has tree nodes
     if (tree_status) {
       hipLaunchKernelGGL(tree_status_ok, dim3((unsigned)((batch + 255) / 256)), dim3(256), 0,
@@ -1792,6 +2125,16 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
     }
   } else if (mfma) {
     hipLaunchKernelGGL((tree_attn_mfma<64, 8, kStages>), grid, dim3(512), 0, st, a);
+  } else if (path == Path::kF32) {
+#define CURE_F32(DD)                                                                                 \
+    do {                                                                                             \
+      if (p.rows_per_wg == 16) hipLaunchKernelGGL((tree_attn_f32<DD, 4>), grid, dim3(256), 0, st, a);      \
+      else if (p.rows_per_wg == 32) hipLaunchKernelGGL((tree_attn_f32<DD, 2>), grid, dim3(256), 0, st, a); \
+      else hipLaunchKernelGGL((tree_attn_f32<DD, 1>), grid, dim3(256), 0, st, a);                    \
+    } while (0)
+    if (d == 128) CURE_F32(128);
+    else CURE_F32(64);
+#undef CURE_F32
   } else {
     if (dtype == CURE_BF16) {
       if (d == 128) hipLaunchKernelGGL((tree_attn_valu<uint16_t, 128>), grid, dim3(256), 0, st, a);

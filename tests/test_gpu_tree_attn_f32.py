@@ -1,0 +1,95 @@
+"""GPU parity of the fp32 matrix-core attention kernel at the edges of its dispatch.
+
+The kernel deals a workgroup's four waves over 64 query rows, or over 32 or 16
+rows and the tile's tokens when a kv-head has no more rows, and takes operands
+that are 16-byte aligned; everything else in fp32 stays on the vector-ALU kernel.
+Outputs against the float64 oracle at the fp32 bars of the other fp32 tests
+(1e-5 output, 1e-4 log-sum-exp: sums of a few hundred fp32 terms of N(0, 1)
+inputs, each rounded at 2^-24).
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2608_00531_amd as pc
+from test_gpu_tree_attn_general import general_tree_workload
+from parity_util import say, upload, gpu_attn, oracle_attn, check_attn
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("hkv,group,nodes", [
+    (2, 1, [1, 3]), (2, 1, [16, 9]), (1, 4, [4, 2]),       # up to 16 rows: tokens over 4 waves
+    (2, 1, [17, 32]), (3, 2, [16, 5]),                     # up to 32 rows: tokens over 2 waves
+    (2, 1, [33, 8]), (2, 4, [16, 15]), (1, 8, [9, 80])])   # rows over 4 waves, row blocks
+@pytest.mark.parametrize("ctx,kv_split", [([0, 31], 0), ([63, 130], 0), ([500, 1], 3), ([257, 640], 0)])
+def test_row_and_token_shares(d, hkv, group, nodes, ctx, kv_split):
+    say("f32", d, hkv, group, nodes, ctx, kv_split)
+    w = general_tree_workload(5, 2, hkv, group, d, nodes, ctx, "nested", dtype="f32")
+    o, lse, st = gpu_attn(w, upload(w), kv_split=kv_split)
+    torch.cuda.synchronize()
+    assert st.tolist() == [pc.CURE_OK] * 2
+    check_attn(w, o, lse, *oracle_attn(w))
+
+
+@pytest.mark.parametrize("scale", [-0.125, 0.0])
+def test_nonpositive_scale(scale):
+    say("f32 scale", scale)
+    w = general_tree_workload(6, 2, 2, 4, 128, [12, 7], [150, 40], "forest", dtype="f32")
+    w.scale = scale
+    o, lse, _ = gpu_attn(w, upload(w))
+    torch.cuda.synchronize()
+    check_attn(w, o, lse, *oracle_attn(w))
+
+
+def test_unaligned_operands_and_bf16_output():
+    """Tensors that start between 16-byte boundaries are taken as before, and a bf16 output is the
+    rounded fp32 one (half an ulp of bf16 plus the fp32 bar)."""
+    w = general_tree_workload(7, 2, 2, 4, 64, [12, 7], [150, 40], "forest", dtype="f32")
+    dev = upload(w)
+    ref_o, ref_l = oracle_attn(w)
+    for name in ("q", "k", "v"):
+        t = torch.empty(dev[name].numel() + 1, device="cuda")[1:].view(dev[name].shape)
+        moved = dict(dev, **{name: t.copy_(dev[name])})
+        assert moved[name].data_ptr() % 16 == 4
+        o, lse, _ = gpu_attn(w, moved)
+        torch.cuda.synchronize()
+        check_attn(w, o, lse, ref_o, ref_l)
+    o, _, _ = gpu_attn(w, dev, out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    for b in range(2):
+        n = int(w.n_nodes[b])
+        err = np.abs(o[b, :n].float().cpu().numpy() - ref_o[b, :n])
+        assert np.all(err <= np.abs(ref_o[b, :n]) * 2.0 ** -8 + 1e-5)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+@pytest.mark.parametrize("group", [1, 2, 8])
+def test_hidden_keys_leave_the_other_nodes_alone(value, group):
+    """An infinite or NaN key of one node reaches only that node and its descendants."""
+    w = general_tree_workload(8, 1, 2, group, 64, [14], [100], "uniform", dtype="f32")
+    parent = w.parent[0]
+    bad = 5
+    sees = np.zeros(14, bool)
+    for i in range(14):
+        sees[i] = i == bad or (parent[i] >= 0 and sees[parent[i]])
+    ref_o, ref_l = oracle_attn(w)
+    w.k[100 + bad] = value
+    o, lse, st = gpu_attn(w, upload(w))
+    torch.cuda.synchronize()
+    assert st.tolist() == [pc.CURE_OK]
+    check_attn(w, o, lse, ref_o, ref_l, sample=[(0, i) for i in range(14) if not sees[i]])
+
+
+def test_malformed_tree_status():
+    w = general_tree_workload(9, 3, 2, 1, 64, [10, 20, 12], [70, 10, 300], "nested", dtype="f32")
+    w.parent[1, 4] = 9
+    dev = upload(w)
+    o, lse, st = gpu_attn(w, dev)
+    torch.cuda.synchronize()
+    assert st.tolist() == [pc.CURE_OK, pc.CURE_ERR_BAD_TREE, pc.CURE_OK]
+    w.parent[1, 4] = 3
+    ref_o, ref_l = oracle_attn(w)
+    check_attn(w, o, lse, ref_o, ref_l, sample=[(b, n) for b in (0, 2) for n in range(int(w.n_nodes[b]))])
