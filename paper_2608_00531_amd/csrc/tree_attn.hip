@@ -43,12 +43,6 @@ constexpr int kTile = 64;            // tokens per K/V tile
 constexpr int kStages = 2;           // K/V tile buffers in the MFMA kernel's LDS ring
 constexpr int kMaxGridY = 65535;     // largest grid y (the split index)
 constexpr int kMinTps = 256;         // tokens per split, at least
-// The fp32 matrix kernel is bound by arithmetic (3.5 us per 64 tokens and wave
-// at head dim 128), so shorter splits pay for their merge earlier: a batch of
-// 4 at 32 nodes takes 39.8 us per call at 64, 128 and 192 tokens (the plan's
-// own split is 192), 46.9 at 256. A block of 16 rows spreads its tokens over
-// four waves and keeps kMinTps.
-constexpr int kMinTpsF32 = 128;
 constexpr int kAncWords = CURE_MAX_TREE_NODES / 64;
 
 struct Args {
@@ -1393,17 +1387,19 @@ void tree_attn_rg(Args a) {
 // and sums: the same precision as the vector-ALU kernel).
 //
 // Bound by the fp32 matrix rate (256 flop per clock and CU; a large fp32 GEMM
-// reaches 137 TFLOP/s on this card), 16 flop of it per K/V byte and query row,
-// so K/V traffic only matters for a few rows per kv-head. A workgroup is four
-// waves, each owning 16 query rows and 1 / WT of every tile's tokens: WT = 1
-// for 64 rows per block, and the waves share a block of 32 or 16 rows by
-// tokens (WT = 2, 4) when a kv-head has no more, so no wave idles; the token
-// shares are combined through LDS at the end. Measured per call against the
-// vector-ALU kernel, which it replaces for aligned operands (its LDS broadcast
-// of every query element per multiply bound it to 11 TFLOP/s): 4 sequences of
-// 850 - 1780 tokens, 32 nodes, 32/8 heads of 128: 257 -> 39.8 us, 70 TFLOP/s
-// with the merge; one sequence of 128 tokens, 12 nodes, 4 heads of 64: 29.2 ->
-// 7.7 us in the kernel.
+// reaches 137 TFLOP/s on this card). A workgroup is four waves over a block of
+// 32 rows (or 16, when a kv-head has no more), each wave owning 16 query rows
+// and 1 / WT of every tile's tokens (WT = 2 or 4), so no wave idles; the token
+// shares are combined through LDS at the end. Small blocks fill two workgroups
+// per CU evenly, which counts for more than reading K/V once per 64 rows (the
+// row blocks of a kv-head share an XCD's L2): blocks of 64 rows (WT = 1) took
+// 46.9 us against 40.3 on the first batch below, 1095 against 948 for 8
+// sequences of 8k tokens and 80 nodes, and only a single 32k sequence gained
+// (158 against 169). Measured per call against the vector-ALU kernel, which it
+// replaces for aligned operands (its LDS broadcast of every query element per
+// multiply bound it to 11 TFLOP/s): 4 sequences of 850 - 1780 tokens, 32 nodes,
+// 32/8 heads of 128: 257 -> 40.3 us, 69 TFLOP/s with the merge; one sequence of
+// 128 tokens, 12 nodes, 4 heads of 64: 29.2 -> 7.7 us in the kernel.
 //
 // Lane l = 16 g + c owns query row c of its wave's 16.
 //   S^T = K Q^T, 16 tokens at a time: MFMA i of column group j (16 columns)
@@ -1421,6 +1417,7 @@ void tree_attn_rg(Args a) {
 // K row that a node does not see leaves its result alone.
 template <int D, int WT>
 struct F32Geo {
+  static_assert(WT == 2 || WT == 4, "two or four token shares");
   static constexpr int kTok = WT == 4 ? 64 : 32;         // tokens per K/V tile
   static constexpr int kTB = kTok / 16 / WT;             // 16-token blocks per wave and tile
   static constexpr int kRows = 64 / WT;                  // query rows per workgroup
@@ -1624,9 +1621,9 @@ void tree_attn_f32(Args a) {
   __builtin_amdgcn_s_waitcnt(0);                   // the trailing out-of-range DMA lands before LDS is reused
   float l_tot = l_run + partner<16>(l_run);
   l_tot = sum_halves(l_tot);
-  if (WT > 1) {
-    // The other token shares of these rows: [wr][wt - 1] records of D + 2
-    // floats per row in the tile buffers, which every wave is done with.
+  {
+    // The other token shares of these rows, a record of D + 2 floats per row
+    // and share in the tile buffers, once every wave is done with those.
     __syncthreads();
     float* s_o = reinterpret_cast<float*>(&s_kv[0][0][0]);
     constexpr int kRec = 64 * (4 * kDBlk + 2);     // floats per wave
@@ -1886,10 +1883,11 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
       p.nw = 8;
       p.rows_per_wg = 32 * p.nw;
     } else if (path == Path::kF32) {
-      // Four waves of 16 rows each; with 32 or 16 rows or fewer the waves
-      // share the rows and split the tokens (F32Geo's WT = 2, 4).
+      // Four waves over 32 rows, two to a row group (F32Geo's WT = 2): the
+      // vector-ALU kernel's blocks, and with two workgroups per CU its splits,
+      // so no call needs more workspace. Up to 16 rows share the tokens four ways.
       p.nw = 4;
-      p.rows_per_wg = rows <= 16 ? 16 : rows <= 32 ? 32 : 64;
+      p.rows_per_wg = rows <= 16 ? 16 : 32;
     } else {
       p.nw = kValuWaves;
       p.rows_per_wg = kValuRows;
@@ -1921,14 +1919,13 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
                              ? F32Geo<128, 4>::kWgsPerCu
                              : 2;
   const int64_t slots = (int64_t)wgs_per_cu * device_cu_count();
-  const int min_tps = path == Path::kF32 && p.rows_per_wg > 16 ? kMinTpsF32 : kMinTps;
-  // The shortest split (at least min_tps tokens) whose workgroups are all
+  // The shortest split (at least kMinTps tokens) whose workgroups are all
   // resident at once, so no workgroup waits for a second round. A batch with
   // more sequence x head pairs than that gets a single split per sequence.
   const auto shortest_resident_split = [&]() {
     const int64_t hi = round_tile(t_max);
     const int64_t lo = round_tile(std::max<int64_t>(
-        min_tps, (t_sum * hkv * p.row_blocks + slots - 1) / std::max<int64_t>(1, slots)));
+        kMinTps, (t_sum * hkv * p.row_blocks + slots - 1) / std::max<int64_t>(1, slots)));
     if (lo >= hi || workgroups(hi) > slots) return hi;
     // workgroups() falls as tps grows: bisect over multiples of the tile.
     int64_t a = lo / kTile, z = hi / kTile;         // workgroups(z * kTile) <= slots
@@ -1940,8 +1937,20 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
     return z * kTile;
   };
   int64_t tps;
+  // fp32 blocks that overfill the chip in single splits may leave most of a
+  // last round idle (640 blocks of 512 slots: 62 % used). Then the bf16 plan's
+  // splits are taken, which spread that round thinner (8 sequences of 8k tokens,
+  // 80 nodes: 948 -> 802 us); the workspace covers them. At head dim 64 a CU
+  // holds three of these workgroups, so the round is not idle (16 sequences of
+  // 500 tokens, 768 blocks: 41 us in single splits, 64 split).
+  const auto fp32_tail_idle = [&]() {
+    const int64_t wgs = workgroups(round_tile(t_max));
+    return path == Path::kF32 && d == 128 && wgs > slots && 5 * wgs < 4 * ((wgs + slots - 1) / slots * slots);
+  };
   if (kv_split > 0) {
     tps = round_tile((t_max + kv_split - 1) / kv_split);
+  } else if (fp32_tail_idle()) {
+    tps = make_plan(batch, hq, hkv, d, n_max, host_ctx_len, host_n_nodes, 0, Path::kBf16).tps;
   } else {
     tps = shortest_resident_split();
     // A small launch (even the shortest splits leave most CUs idle, as for one
@@ -2126,15 +2135,13 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
   } else if (mfma) {
     hipLaunchKernelGGL((tree_attn_mfma<64, 8, kStages>), grid, dim3(512), 0, st, a);
   } else if (path == Path::kF32) {
-#define CURE_F32(DD)                                                                                 \
-    do {                                                                                             \
-      if (p.rows_per_wg == 16) hipLaunchKernelGGL((tree_attn_f32<DD, 4>), grid, dim3(256), 0, st, a);      \
-      else if (p.rows_per_wg == 32) hipLaunchKernelGGL((tree_attn_f32<DD, 2>), grid, dim3(256), 0, st, a); \
-      else hipLaunchKernelGGL((tree_attn_f32<DD, 1>), grid, dim3(256), 0, st, a);                    \
-    } while (0)
-    if (d == 128) CURE_F32(128);
-    else CURE_F32(64);
-#undef CURE_F32
+    if (d == 128) {
+      if (p.rows_per_wg == 16) hipLaunchKernelGGL((tree_attn_f32<128, 4>), grid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((tree_attn_f32<128, 2>), grid, dim3(256), 0, st, a);
+    } else {
+      if (p.rows_per_wg == 16) hipLaunchKernelGGL((tree_attn_f32<64, 4>), grid, dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((tree_attn_f32<64, 2>), grid, dim3(256), 0, st, a);
+    }
   } else {
     if (dtype == CURE_BF16) {
       if (d == 128) hipLaunchKernelGGL((tree_attn_valu<uint16_t, 128>), grid, dim3(256), 0, st, a);
