@@ -1,0 +1,56 @@
+"""GPU parity of the margin pass on rows that start anywhere.
+
+A row length or a base address that is no multiple of 16 bytes puts each row's
+first 16-byte boundary at another entry. The vectors start there; the entries
+before and after them are taken singly. Every base offset of a 16-byte window,
+vocabularies around the vector, chunk and loop-step sizes, with the best
+entries in the first and last positions of the row and at the chunk edges,
+against the oracle: indices bit-exact.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2608_00531_amd as pc
+from synth.workloads import bf16_round
+from parity_util import say, MARGIN_TOL
+
+pytestmark = pytest.mark.gpu
+
+
+def shifted(a, dtype, off):
+    """`a` on the GPU, its first element `off` elements past a 16-byte boundary."""
+    t = torch.from_numpy(np.ascontiguousarray(a).view(np.int16 if dtype == "bf16" else np.float32))
+    buf = torch.zeros(t.numel() + 16, dtype=t.dtype, device="cuda")
+    assert buf.data_ptr() % 16 == 0
+    x = buf[off:off + t.numel()].view(a.shape).copy_(t)
+    return x.view(torch.bfloat16) if dtype == "bf16" else x
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("vocab", [2, 5, 9, 17, 8191, 8200, 16385, 50257, 70001])
+def test_margins_on_rows_that_start_anywhere(dtype, vocab):
+    rng = np.random.default_rng(vocab)
+    rows = 24
+    x = rng.standard_normal((rows, vocab)).astype(np.float32)
+    edges = [0, 1, 6, 7, 8, 9, vocab // 2, vocab - 9, vocab - 8, vocab - 2, vocab - 1]
+    for r in range(rows - 4):                       # the last rows keep the noise's own order
+        i, j = rng.choice([e for e in edges if 0 <= e < vocab], 2)
+        x[r, i] = 8.0
+        x[r, j] = 8.0 if r % 3 == 0 else 9.0       # ties too
+    x[0, :] = -np.inf
+    x[0, vocab - 1] = 1.0
+    bits = bf16_round(x) if dtype == "bf16" else x
+    if dtype == "bf16":
+        bits[0, :vocab - 1] = 0xff80                # -inf (the rounding helper takes finite values)
+    ref = oracle.margins(bits, dtype)
+    for off in range(8 if dtype == "bf16" else 4):
+        say("margins", dtype, vocab, "offset", off)
+        got = pc.cure_margins(shifted(bits[None], dtype, off), chain_len=rows, repair_budget=8)
+        torch.cuda.synchronize()
+        for k in ("top1_idx", "top2_idx", "top1_val", "top2_val"):
+            assert np.array_equal(got[k][0].cpu().numpy(), ref[k]), (k, off)
+        err = np.abs(got["lse"][0].cpu().numpy() - ref["lse"])
+        assert np.max(err) <= MARGIN_TOL
