@@ -1,4 +1,4 @@
-"""GPU parity of the margin pass on rows that start anywhere.
+"""GPU parity of the margin pass and the repair tree on rows that start anywhere.
 
 A row length or a base address that is no multiple of 16 bytes puts each row's
 first 16-byte boundary at another entry. The vectors start there; the entries
@@ -14,8 +14,10 @@ import torch
 
 import oracle
 import paper_2608_00531_amd as pc
+from synth import make_draft_block
 from synth.workloads import bf16_round
 from parity_util import say, MARGIN_TOL
+from test_gpu_repair import run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +56,17 @@ def test_margins_on_rows_that_start_anywhere(dtype, vocab):
             assert np.array_equal(got[k][0].cpu().numpy(), ref[k]), (k, off)
         err = np.abs(got["lse"][0].cpu().numpy() - ref["lse"])
         assert np.max(err) <= MARGIN_TOL
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("vocab", [9, 16, 23, 8192, 8193, 8199, 16384, 32001])
+def test_repair_trees_on_rows_that_start_anywhere(dtype, vocab):
+    blk = make_draft_block(batch=2, chain_len=6, vocab=vocab, dtype=dtype, seed=vocab % 89, n_low=4,
+                           runners=min(6, vocab - 1), depth=2)
+    if vocab > 100:                                 # equal values beyond a wave's list: the long way round
+        blk.logits[0, 2, :300] = blk.logits[0, 2].max() if dtype == "f32" else bf16_round(
+            np.float32([40.0]))[0]
+    for off in range(8 if dtype == "bf16" else 4):
+        say("repair", dtype, vocab, "offset", off)
+        run_case(blk, tau=1.5, budget=16, depth=2, scale=1.0, b_min=1, b_max=5,
+                 logits_dev=shifted(blk.logits, dtype, off))
