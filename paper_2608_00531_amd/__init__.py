@@ -1,7 +1,7 @@
 """libcure: MI355X (gfx950) HIP kernels for CURE's verify-and-repair hot path.
 
 The kernels and the C ABI live in csrc/ and include/cure.h; ``cure`` is the
-thin ctypes binding (names match the C entry points).
+thin Python binding (names match the C entry points).
 """
 
 from .cure import (  # noqa: F401

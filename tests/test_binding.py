@@ -1,0 +1,96 @@
+"""The Python binding's argument handling: errors without a GPU, and the forms that
+each argument is taken in."""
+
+import threading
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2608_00531_amd as pc
+
+
+def test_cpu_tensors_and_wrong_objects_are_refused():
+    x = torch.zeros(1, 4, 16)
+    i = torch.zeros(1, 4, dtype=torch.int32)
+    n = torch.full((1,), 4, dtype=torch.int32)
+    for call in (lambda: pc.cure_margins(x), lambda: pc.cure_margins_noalloc(x),
+                 lambda: pc.cure_margins_accept(x, i, i, n, n, 4),
+                 lambda: pc.cure_accept(i, i, i, n, n, 4),
+                 lambda: pc.cure_repair_tree(x, x[..., 0], i, n, i, 4, 2, 1.0),
+                 lambda: pc.cure_commit(x, x, n.long(), n, n, i, n, i, n, 4),
+                 lambda: pc.cure_tree_attn(x, x, x, n.long(), n, n, i, [1], [4], 1.0)):
+        with pytest.raises(pc.CureError, match="must live on the GPU"):
+            call()
+    with pytest.raises(TypeError):
+        pc.cure_margins("logits")
+
+
+def _attention(host_ctx, host_nodes, **kw):
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q = torch.randn(2, 3, 4, 64, generator=g, device="cuda")
+    k = torch.randn(2 * 43, 2, 64, generator=g, device="cuda")
+    i32 = dict(dtype=torch.int32, device="cuda")
+    return pc.cure_tree_attn(q, k, k, torch.tensor([0, 43], device="cuda"),
+                             torch.tensor([40, 40], **i32), torch.tensor([3, 3], **i32),
+                             torch.tensor([[-1, 0, 1]] * 2, **i32), host_ctx, host_nodes, 0.125, **kw)
+
+
+@pytest.mark.gpu
+def test_host_sizes_in_every_form():
+    o, lse, st = _attention([40, 40], [3, 3])
+    assert lse.shape == (2, 3, 4) and lse.dtype == torch.float32 and st.tolist() == [0, 0]
+    for ctx in ((40, 40), np.array([40, 40]), np.array([40, 40], np.int32), [np.int64(40), 40],
+                torch.tensor([40, 40]), np.array([40, 0, 40, 0], np.int32)[::2]):
+        assert torch.equal(_attention(ctx, [3, 3])[0], o)
+    assert _attention([40, 40], [3, 3], with_lse=False)[1] is None
+    assert _attention([40, 40], [3, 3], out_dtype=torch.bfloat16)[0].dtype == torch.bfloat16
+    with pytest.raises(pc.CureError, match="shorter than the batch"):
+        _attention([40], [3, 3])
+    with pytest.raises(pc.CureError, match="CURE_ERR_INVALID_ARG"):
+        _attention([40, -1], [3, 3])
+    with pytest.raises(pc.CureError, match="unsupported dtype torch.float16"):
+        _attention([40, 40], [3, 3], out_dtype=torch.float16)
+
+
+@pytest.mark.gpu
+def test_logits_views_and_scalar_forms():
+    x = torch.randn(3, 5, 4099, device="cuda")
+    want = pc.cure_margins(x, 5, 1.5, 4, 2)
+    for view in (x.transpose(0, 1).contiguous().transpose(0, 1),
+                 torch.cat([x, x], dim=2)[..., :4099]):
+        got = pc.cure_margins(view, chain_len=np.int64(5), tau=torch.tensor(1.5), repair_budget=True + 3,
+                              branch_depth=np.int32(2))
+        assert set(got) == set(want)
+        assert all(torch.equal(got[k], want[k]) for k in want)
+    flat = pc.cure_margins(x[0], gate=False)
+    assert flat["lse"].shape == (1, 5) and "ufp_pos" not in flat
+    assert torch.equal(flat["lse"][0], want["lse"][0])
+    with pytest.raises(TypeError):
+        pc.cure_margins(x, chain_len=5.0)
+    with pytest.raises(ValueError):
+        pc.cure_margins(x[0, 0])
+    with pytest.raises(pc.CureError, match="unsupported dtype torch.float64"):
+        pc.cure_margins(x.double())
+
+
+@pytest.mark.gpu
+def test_threads_on_streams_of_their_own():
+    """Calls of several threads, each on its own stream and with workspaces that grow between calls."""
+    xs = [torch.randn(b, 16, 40000, device="cuda") for b in (1, 2, 4, 8)]
+    want = [pc.cure_margins(x, 16, repair_budget=8, branch_depth=2) for x in xs]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work():
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for x, w in zip(xs, want):
+                got = pc.cure_margins(x, 16, repair_budget=8, branch_depth=2)
+                wrong.extend(k for k in w if not torch.equal(got[k], w[k]))
+
+    threads = [threading.Thread(target=work) for _ in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
