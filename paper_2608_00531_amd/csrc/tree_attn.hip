@@ -43,6 +43,7 @@ constexpr int kTile = 64;            // tokens per K/V tile
 constexpr int kStages = 2;           // K/V tile buffers in the MFMA kernel's LDS ring
 constexpr int kMaxGridY = 65535;     // largest grid y (the split index)
 constexpr int kMinTps = 256;         // tokens per split, at least
+constexpr int kMaxUnits = 512;       // entries of a compact launch's table
 constexpr int kAncWords = CURE_MAX_TREE_NODES / 64;
 
 struct Args {
@@ -63,6 +64,42 @@ struct Args {
   float* part_o;                     // [batch][hq][n_max][max_splits][d]
   float* part_lse;                   // [batch][hq][n_max][max_splits]
 };
+
+// Arguments of a compact launch (see locate()).
+struct CompactArgs : Args {
+  int32_t row_blocks;
+  uint32_t unit[kMaxUnits / 2];      // unit u in half u % 2 of word u / 2: sequence | split << 6
+  int32_t seq_splits[64];            // splits the host gave each sequence
+};
+
+// Where a workgroup works: kv-head hk, row block rb and split s of sequence b,
+// and the most splits that sequence may have.
+struct Place {
+  int b, hk, rb, s, max_splits;
+};
+
+// Full launches are a 3-D grid, (kv-heads x row blocks, splits, batch), in which a
+// ragged batch leaves workgroups without work. Each of those still takes its turn
+// when the dispatcher deals workgroups to the shader engines, so some engines are
+// dealt more real ones than they have CUs for, and those start when the first
+// have finished: on 16 sequences of 1k to 4k tokens (48 nodes, 256 of 384
+// workgroups real) the longest workgroup ran 44 us and the kernel 58. A compact
+// launch holds (kv-heads x row blocks) x the units the host counted, from a table
+// in the kernel arguments: read by the scalar unit with the other arguments.
+CURE_DEV Place locate(const Args& a) {
+  return Place{(int)blockIdx.z, (int)(blockIdx.x % a.hkv), (int)(blockIdx.x / a.hkv), (int)blockIdx.y, a.max_splits};
+}
+CURE_DEV Place locate(const CompactArgs& a) {
+  const int blocks = a.hkv * a.row_blocks;
+  const int u = blockIdx.x / blocks, x = blockIdx.x - u * blocks;
+  const int e = (a.unit[u >> 1] >> (16 * (u & 1))) & 0xffff;
+  const int b = e & 63;
+  return Place{b, x % a.hkv, x / a.hkv, e >> 6, a.seq_splits[b]};
+}
+
+// The most splits sequence b may have, for the merge.
+CURE_DEV int max_splits_of(const Args& a, int) { return a.max_splits; }
+CURE_DEV int max_splits_of(const CompactArgs& a, int b) { return a.seq_splits[b]; }
 
 // Number of context splits of a sequence with T = ctx + nodes rows. The last
 // split runs to T, so a clamp never drops rows.
@@ -410,8 +447,8 @@ struct TileGeo {
 constexpr int waitcnt_vm(int vm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4); }
 constexpr uint32_t kOobOffset = 0x80000000u;   // past any sequence's buffer resource
 
-template <int D, int NW, int NBUF>
-__global__ __launch_bounds__(64 * NW, NBUF > 2 ? 1 : 2) void tree_attn_mfma(Args a) {
+template <int D, int NW, int NBUF, class A>
+__global__ __launch_bounds__(64 * NW, NBUF > 2 ? 1 : 2) void tree_attn_mfma(A a) {
   using G = TileGeo<D>;
   constexpr int kKSteps = D / 16;                  // MFMA k-steps for Q K^T
   constexpr int kDBlk = D / 32;                    // 32-column blocks of O^T
@@ -428,10 +465,8 @@ __global__ __launch_bounds__(64 * NW, NBUF > 2 ? 1 : 2) void tree_attn_mfma(Args
   __shared__ __attribute__((aligned(1024))) unsigned char s_k[NBUF][G::kTileBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char s_v[NBUF][G::kTileBytes];
 
-  const int b = blockIdx.z;
-  const int hk = blockIdx.x % a.hkv;
-  const int rb = blockIdx.x / a.hkv;
-  const int s = blockIdx.y;
+  const Place at = locate(a);
+  const int b = at.b, hk = at.hk, rb = at.rb, s = at.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
 
@@ -466,7 +501,7 @@ __global__ __launch_bounds__(64 * NW, NBUF > 2 ? 1 : 2) void tree_attn_mfma(Args
   asm volatile("" : : "s"(n_raw), "s"(L), "s"(off));
   const int N = min(n_raw, a.n_max);
   const int T = L + N;
-  const int S = split_count(T, N, a.tps, a.max_splits);
+  const int S = split_count(T, N, a.tps, at.max_splits);
   const int rows = N * a.group;
   if (S == 0) {                         // no nodes: nothing to compute; the empty tree is valid
     report_tree(a, b, true, s == 0 && hk == 0 && rb == 0);
@@ -728,8 +763,8 @@ __global__ __launch_bounds__(64 * NW, NBUF > 2 ? 1 : 2) void tree_attn_mfma(Args
 //     D register r = O column 16 db + 4 g + r of row c
 // At most 128 VGPRs (four waves per SIMD): two 8-wave workgroups share a CU
 // whenever a launch has more workgroups than CUs.
-template <int D, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void tree_attn_m16(Args a) {
+template <int D, int NW, class A>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void tree_attn_m16(A a) {
   using G = TileGeo<D>;
   constexpr int kKSteps = D / 32;                  // k-steps for Q K^T
   constexpr int kDBlk = D / 16;                    // 16-column blocks of O^T
@@ -746,10 +781,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
   __shared__ __attribute__((aligned(1024))) unsigned char s_k[2][G::kTileBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char s_v[2][G::kTileBytes];
 
-  const int b = blockIdx.z;
-  const int hk = blockIdx.x % a.hkv;
-  const int rb = blockIdx.x / a.hkv;
-  const int s = blockIdx.y;
+  const Place at = locate(a);
+  const int b = at.b, hk = at.hk, rb = at.rb, s = at.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 15, g = lane >> 4;
 
@@ -779,7 +812,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
   asm volatile("" : : "s"(n_raw), "s"(L), "s"(off));
   const int N = min(n_raw, a.n_max);
   const int T = L + N;
-  const int S = split_count(T, N, a.tps, a.max_splits);
+  const int S = split_count(T, N, a.tps, at.max_splits);
   const int rows = N * a.group;
   if (S == 0) {                         // no nodes: nothing to compute; the empty tree is valid
     report_tree(a, b, true, s == 0 && hk == 0 && rb == 0);
@@ -1026,9 +1059,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
 // runs the tile loop's body instantiated for its own group count. Row r of a
 // wave's group rg is query row rb * rows_per_wg + 16 (first + rg) + c, with
 // first the wave's first group (lane l = 16 g + c as in the 16-row kernel).
-template <int D, int NW, int RG, int NBUF, int NDMA, int HT, int WPE>
+template <int D, int NW, int RG, int NBUF, int NDMA, int HT, int WPE, class A>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
-void tree_attn_rg(Args a) {
+void tree_attn_rg(A a) {
   using G = TileGeo<D>;
   constexpr int kKSteps = D / 32;                  // k-steps for Q K^T
   constexpr int kDBlk = D / 16;                    // 16-column blocks of O^T
@@ -1055,10 +1088,8 @@ void tree_attn_rg(Args a) {
   __shared__ __attribute__((aligned(1024))) unsigned char s_k[NBUF][G::kTileBytes];
   __shared__ __attribute__((aligned(1024))) unsigned char s_v[NBUF][G::kTileBytes];
 
-  const int b = blockIdx.z;
-  const int hk = blockIdx.x % a.hkv;
-  const int rb = blockIdx.x / a.hkv;
-  const int s = blockIdx.y;
+  const Place at = locate(a);
+  const int b = at.b, hk = at.hk, rb = at.rb, s = at.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 15, g = lane >> 4;
   const int groups_wg = (a.rows_per_wg + 15) / 16;
@@ -1094,7 +1125,7 @@ void tree_attn_rg(Args a) {
   asm volatile("" : : "s"(n_raw), "s"(L), "s"(off));
   const int N = min(n_raw, a.n_max);
   const int T = L + N;
-  const int S = split_count(T, N, a.tps, a.max_splits);
+  const int S = split_count(T, N, a.tps, at.max_splits);
   const int rows = N * a.group;
   if (S == 0) {                         // no nodes: nothing to compute; the empty tree is valid
     report_tree(a, b, true, s == 0 && hk == 0 && rb == 0);
@@ -1428,9 +1459,9 @@ struct F32Geo {
   static CURE_DEV int offset(int row, int chunk) { return row * kRowBytes + ((chunk ^ (row & 15)) << 4); }
 };
 
-template <int D, int WT>
+template <int D, int WT, class A>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((F32Geo<D, WT>::kWgsPerCu))))
-void tree_attn_f32(Args a) {
+void tree_attn_f32(A a) {
   using G = F32Geo<D, WT>;
   constexpr int kTB = G::kTB;
   constexpr int kKGroups = D / 16;                 // 16-column groups of Q K^T
@@ -1442,10 +1473,8 @@ void tree_attn_f32(Args a) {
   __shared__ int s_bad;
   __shared__ __attribute__((aligned(1024))) unsigned char s_kv[2][2][G::kTileBytes];  // [buffer][K, V]
 
-  const int b = blockIdx.z;
-  const int hk = blockIdx.x % a.hkv;
-  const int rb = blockIdx.x / a.hkv;
-  const int s = blockIdx.y;
+  const Place at = locate(a);
+  const int b = at.b, hk = at.hk, rb = at.rb, s = at.s;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 15, g = lane >> 4;
   const int wt = wave % WT, wr = wave / WT;        // this wave's share of the tokens and its rows
@@ -1471,7 +1500,7 @@ void tree_attn_f32(Args a) {
   asm volatile("" : : "s"(n_raw), "s"(L), "s"(off));
   const int N = min(n_raw, a.n_max);
   const int T = L + N;
-  const int S = split_count(T, N, a.tps, a.max_splits);
+  const int S = split_count(T, N, a.tps, at.max_splits);
   const int rows = N * a.group;
   if (S == 0) {                         // no nodes: nothing to compute; the empty tree is valid
     report_tree(a, b, true, s == 0 && hk == 0 && rb == 0);
@@ -1697,8 +1726,8 @@ void tree_attn_f32(Args a) {
 // first and each row reads only its own splits' slots, instead of fetching
 // slots it would discard. The lane groups holding different splits are
 // combined with xor shuffles at the end.
-template <int D, int NB, bool kOwnSplits>
-__global__ __launch_bounds__(256) void attn_merge(Args a) {
+template <int D, int NB, bool kOwnSplits, class A>
+__global__ __launch_bounds__(256) void attn_merge(A a) {
   constexpr int kLanesPerSplit = D / 4;
   constexpr int kSplitsPerLoad = kWave / kLanesPerSplit;
   constexpr int kSplitsPerBatch = kSplitsPerLoad * NB;
@@ -1733,7 +1762,7 @@ __global__ __launch_bounds__(256) void attn_merge(Args a) {
   const int L = a.ctx_len[b];
   const int N = min(n_raw, a.n_max);
   if (n >= N) return;
-  const int S = split_count(L + N, N, a.tps, a.max_splits);
+  const int S = split_count(L + N, N, a.tps, max_splits_of(a, b));
   if (S <= 1) return;
   if (kOwnSplits) {
     load_batch(0, S);
@@ -2080,7 +2109,7 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
   if (need > 0 && (!workspace || workspace_bytes < need)) return CURE_ERR_WORKSPACE;
   if ((size_t)p.row_blocks * hkv > 65535 || batch > 65535) return CURE_ERR_UNSUPPORTED;
 
-  Args a{};
+  CompactArgs a{};                      // its Args part serves full launches
   a.q = q;
   a.k = k;
   a.v = v;
@@ -2121,46 +2150,63 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
   // KV heads (and row blocks) vary fastest: consecutive workgroups, which the
   // dispatcher spreads over the XCDs and starts together, read the heads of
   // the same token range, so concurrent reads cover whole cache rows.
-  const dim3 grid(hkv * p.row_blocks, p.max_splits, batch);
-  if (p.rows48) {
-    hipLaunchKernelGGL((tree_attn_rg<128, kRg3Waves, 3, 2, 4, 2, 2>), grid, dim3(64 * kRg3Waves), 0,
-                       st, a);
-  } else if (p.rows16) {
-    if (d == 128) {
-      if (p.nw == 8) hipLaunchKernelGGL((tree_attn_m16<128, 8>), grid, dim3(512), 0, st, a);
-      else hipLaunchKernelGGL((tree_attn_m16<128, 16>), grid, dim3(1024), 0, st, a);
-    } else {
-      hipLaunchKernelGGL((tree_attn_m16<64, 8>), grid, dim3(512), 0, st, a);
+  dim3 grid(hkv * p.row_blocks, p.max_splits, batch);
+  // A ragged batch of up to 64 sequences is launched compactly (locate()).
+  bool compact = path != Path::kValu && !p.uniform_splits && batch <= 64 && p.max_splits < 1024;
+  if (compact) {
+    int units = 0;
+    for (int b = 0; b < batch && compact; ++b) {
+      const int N = std::min(host_n_nodes[b], n_max);
+      const int64_t T = (int64_t)host_ctx_len[b] + N;
+      // A sequence without nodes has one unit, which reports its status.
+      const int splits = N > 0 ? (int)((T + p.tps - 1) / p.tps) : 1;
+      compact = units + splits <= kMaxUnits;
+      for (int i = 0; i < splits && compact; ++i, ++units)
+        a.unit[units >> 1] |= (uint32_t)(b | i << 6) << (16 * (units & 1));
+      a.seq_splits[b] = splits;
     }
-  } else if (mfma) {
-    hipLaunchKernelGGL((tree_attn_mfma<64, 8, kStages>), grid, dim3(512), 0, st, a);
-  } else if (path == Path::kF32) {
-    if (d == 128) {
-      if (p.rows_per_wg == 16) hipLaunchKernelGGL((tree_attn_f32<128, 4>), grid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((tree_attn_f32<128, 2>), grid, dim3(256), 0, st, a);
-    } else {
-      if (p.rows_per_wg == 16) hipLaunchKernelGGL((tree_attn_f32<64, 4>), grid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((tree_attn_f32<64, 2>), grid, dim3(256), 0, st, a);
-    }
-  } else {
-    if (dtype == CURE_BF16) {
-      if (d == 128) hipLaunchKernelGGL((tree_attn_valu<uint16_t, 128>), grid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((tree_attn_valu<uint16_t, 64>), grid, dim3(256), 0, st, a);
-    } else {
-      if (d == 128) hipLaunchKernelGGL((tree_attn_valu<float, 128>), grid, dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((tree_attn_valu<float, 64>), grid, dim3(256), 0, st, a);
-    }
+    a.row_blocks = p.row_blocks;
+    compact = compact && (int64_t)units * hkv * p.row_blocks <= INT32_MAX;
+    if (compact) grid = dim3((unsigned)(units * hkv * p.row_blocks));
   }
+  const Args& full = a;
+#define CURE_ATTN(threads, kernel, ...)                                                                    \
+  do {                                                                                                     \
+    if (compact) hipLaunchKernelGGL((kernel<__VA_ARGS__, CompactArgs>), grid, dim3(threads), 0, st, a);    \
+    else hipLaunchKernelGGL((kernel<__VA_ARGS__, Args>), grid, dim3(threads), 0, st, full);                \
+  } while (0)
+  if (p.rows48) {
+    CURE_ATTN(64 * kRg3Waves, tree_attn_rg, 128, kRg3Waves, 3, 2, 4, 2, 2);
+  } else if (p.rows16) {
+    if (d == 128 && p.nw == 8) CURE_ATTN(512, tree_attn_m16, 128, 8);
+    else if (d == 128) CURE_ATTN(1024, tree_attn_m16, 128, 16);
+    else CURE_ATTN(512, tree_attn_m16, 64, 8);
+  } else if (mfma) {
+    CURE_ATTN(512, tree_attn_mfma, 64, 8, kStages);
+  } else if (path == Path::kF32) {
+    if (d == 128 && p.rows_per_wg == 16) CURE_ATTN(256, tree_attn_f32, 128, 4);
+    else if (d == 128) CURE_ATTN(256, tree_attn_f32, 128, 2);
+    else if (p.rows_per_wg == 16) CURE_ATTN(256, tree_attn_f32, 64, 4);
+    else CURE_ATTN(256, tree_attn_f32, 64, 2);
+  } else if (dtype == CURE_BF16) {
+    if (d == 128) hipLaunchKernelGGL((tree_attn_valu<uint16_t, 128>), grid, dim3(256), 0, st, full);
+    else hipLaunchKernelGGL((tree_attn_valu<uint16_t, 64>), grid, dim3(256), 0, st, full);
+  } else {
+    if (d == 128) hipLaunchKernelGGL((tree_attn_valu<float, 128>), grid, dim3(256), 0, st, full);
+    else hipLaunchKernelGGL((tree_attn_valu<float, 64>), grid, dim3(256), 0, st, full);
+  }
+#undef CURE_ATTN
   if (hipGetLastError() != hipSuccess) return CURE_ERR_HIP;
   if (p.max_splits > 1) {
     const dim3 mgrid((unsigned)((hq + 3) / 4), (unsigned)n_max, (unsigned)batch);
     const int per_load = 256 / d;                       // splits per merge load
     const int nb = p.max_splits <= 2 * per_load ? 2 : p.max_splits <= 4 * per_load ? 4 : 8;
     const bool own = !p.uniform_splits;
-#define CURE_MERGE(DD, NN)                                                                   \
-    do {                                                                                     \
-      if (own) hipLaunchKernelGGL((attn_merge<DD, NN, true>), mgrid, dim3(256), 0, st, a);   \
-      else hipLaunchKernelGGL((attn_merge<DD, NN, false>), mgrid, dim3(256), 0, st, a);      \
+#define CURE_MERGE(DD, NN)                                                                                   \
+    do {                                                                                                     \
+      if (compact) hipLaunchKernelGGL((attn_merge<DD, NN, true, CompactArgs>), mgrid, dim3(256), 0, st, a);  \
+      else if (own) hipLaunchKernelGGL((attn_merge<DD, NN, true, Args>), mgrid, dim3(256), 0, st, full);     \
+      else hipLaunchKernelGGL((attn_merge<DD, NN, false, Args>), mgrid, dim3(256), 0, st, full);             \
     } while (0)
     if (d == 128) {
       if (nb == 2) CURE_MERGE(128, 2);

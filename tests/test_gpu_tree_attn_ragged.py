@@ -1,0 +1,72 @@
+"""GPU parity of ragged attention launches, which hold only the workgroups with work.
+
+The host lists each sequence's splits in the kernel arguments (up to 64 sequences
+and 512 splits in all); other launches are a grid over sequences and splits. Both
+forms against the float64 oracle: at the limits of the list, with sequences
+without nodes or context, with forced split counts, for every kernel family, and
+with host sizes that are not the device's (they only plan the launch, so any
+nonnegative ones within n_max have to give the same result).
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2608_00531_amd as pc
+from test_gpu_tree_attn_general import general_tree_workload
+from parity_util import say, upload, gpu_attn, oracle_attn, check_attn
+
+pytestmark = pytest.mark.gpu
+
+
+def check(w, dev, ref, **kw):
+    o, lse, st = gpu_attn(w, dev, **kw)
+    torch.cuda.synchronize()
+    assert st.tolist() == [pc.CURE_OK] * w.batch
+    check_attn(w, o, lse, *ref)
+
+
+@pytest.mark.parametrize("dtype,hkv,group,d,nodes", [
+    ("bf16", 2, 4, 128, [16, 9, 0, 16, 3]), ("bf16", 1, 4, 128, [48, 40, 48, 0, 33]),
+    ("bf16", 1, 4, 128, [80, 80, 65, 10, 0]), ("bf16", 2, 4, 128, [120, 4, 0, 100, 77]),
+    ("bf16", 3, 2, 64, [20, 0, 7, 20, 20]), ("bf16", 1, 4, 64, [48, 30, 48, 0, 11]),
+    ("f32", 2, 4, 64, [12, 0, 12, 5, 1]), ("f32", 1, 1, 128, [9, 16, 2, 0, 16])])
+@pytest.mark.parametrize("kv_split", [0, 5])
+def test_every_kernel_family(dtype, hkv, group, d, nodes, kv_split):
+    say("ragged", dtype, hkv, group, d, nodes, kv_split)
+    ctx = [700, 0, 300, 1500, 65]
+    w = general_tree_workload(21, 5, hkv, group, d, nodes, ctx, "nested", dtype=dtype)
+    check(w, upload(w), oracle_attn(w), kv_split=kv_split)
+
+
+@pytest.mark.parametrize("batch", [63, 64, 65])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_batches_around_the_list_of_sequences(batch, dtype):
+    rng = np.random.default_rng(batch)
+    ctx = [int(c) for c in rng.integers(0, 900, batch)]
+    nodes = [int(n) for n in rng.integers(0, 9, batch)]
+    nodes[-1], ctx[-1] = 8, 899
+    w = general_tree_workload(22, batch, 1, 4, 64, nodes, ctx, "uniform", dtype=dtype)
+    check(w, upload(w), oracle_attn(w))
+
+
+@pytest.mark.parametrize("kv_split", [100, 200])
+def test_more_splits_than_the_list_holds(kv_split):
+    # Sequences of 12800 and about 6400 tokens in 64- or 128-token splits: 350 and 700 splits.
+    w = general_tree_workload(23, 4, 1, 2, 64, [6, 6, 3, 6], [12790, 6400, 6390, 6300], "uniform")
+    check(w, upload(w), oracle_attn(w), kv_split=kv_split)
+
+
+@pytest.mark.parametrize("dtype,group", [("bf16", 4), ("f32", 2)])
+@pytest.mark.parametrize("host", ["larger", "smaller", "swapped", "none_here"])
+def test_host_sizes_only_plan(dtype, group, host):
+    ctx, nodes = [700, 300, 1500, 65], [16, 12, 16, 5]
+    w = general_tree_workload(24, 4, 2, group, 128, nodes, ctx, "forest", dtype=dtype)
+    dev, ref = upload(w), oracle_attn(w)
+    hc, hn = {"larger": ([2000, 900, 1600, 900], [16] * 4), "smaller": ([300, 20, 700, 0], [3, 1, 16, 5]),
+              "swapped": (ctx[::-1], nodes[::-1]), "none_here": ([700, 300, 1500, 65], [0, 12, 16, 0])}[host]
+    o, lse, st = pc.cure_tree_attn(dev["q"], dev["k"], dev["v"], dev["kv_off"], dev["ctx_len"], dev["n_nodes"],
+                                   dev["parent"], hc, hn, w.scale)
+    torch.cuda.synchronize()
+    assert st.tolist() == [pc.CURE_OK] * 4
+    check_attn(w, o, lse, *ref)
