@@ -1844,6 +1844,89 @@ __global__ __launch_bounds__(256) void attn_merge(A a) {
       wsum > 0.f ? m + logf(wsum) : -INFINITY;
 }
 
+// ---------------------------------------------------------------------------
+// LSE merge of launches with at most four splits: D / 4 lanes per output row (b, n,
+// head), each holding four columns of every split's partial row, so a wave covers
+// two rows at head dim 128 and four at 64 and combines them without any exchange
+// between lanes. Every split's loads are issued before the sequence's sizes have
+// arrived (the launch says how many splits the sequence may have; slots past its
+// own count on the device are masked out).
+//
+// Bound by the partials' round trips, so by how many waves of them there are: a
+// wave per row takes several rounds once a launch has more rows than the chip
+// holds waves (8192), which is what large launches with few splits have. Per
+// call, wave per row and here: ragged batch (3 splits, 24.6k rows) 59.8 and
+// 57.9 us, 80-node trees of 8 sequences (4 splits, 20.5k rows) 102.5 and 101.1,
+// head dim 64 (2 splits, 24.6k rows) 33.3 and 32.3, (16.4k rows) 35.8 and 35.1.
+// With fewer rows or more splits the wave per row is ahead, as it spreads a row's
+// loads over more lanes: fp32 (8.2k rows) 46.4 and 47.1, 2 sequences (2k rows)
+// 11.3 and 12.7; 32k context (8 splits) 105.5 and 106.8, head dim 64 (11
+// splits) 30.3 and 34.2.
+constexpr int kFewSplits = 4;
+constexpr int64_t kManyRows = 16384;
+static_assert(kFewSplits == 4, "instantiated for two and four splits");
+
+template <int D, int NB, class A>
+__global__ __launch_bounds__(256) void attn_merge_few(A a) {
+  constexpr int kLanes = D / 4;
+  constexpr int kRows = 256 / kLanes;
+  // Grid (heads / kRows, n_max, batch): the row's coordinates come straight from
+  // the block index (no 64-bit divisions).
+  const int head = blockIdx.x * kRows + threadIdx.x / kLanes;
+  const int col = (threadIdx.x % kLanes) * 4;
+  const int n = blockIdx.y;
+  const int b = blockIdx.z;
+  if (head >= a.hq) return;
+  const int64_t p0 = part_index(a, b, head, n, 0);
+  const int slots = max_splits_of(a, b);
+  float4 v[NB];
+  float l[NB];
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const bool ok = u < slots;
+    v[u] = ok ? *reinterpret_cast<const float4*>(a.part_o + (p0 + u) * D + col)
+              : make_float4(0.f, 0.f, 0.f, 0.f);
+    l[u] = ok ? a.part_lse[p0 + u] : -INFINITY;
+  }
+  const int n_raw = a.n_nodes[b];
+  const int L = a.ctx_len[b];
+  const int N = min(n_raw, a.n_max);
+  if (n >= N) return;
+  const int S = split_count(L + N, N, a.tps, slots);
+  if (S <= 1) return;
+  // Slots past the count hold stale data (the plan comes from host copies of the
+  // sizes): no weight, and no value that could turn one into a NaN.
+  float m = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    if (u >= S) {
+      v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      l[u] = -INFINITY;
+    }
+    m = fmaxf(m, l[u]);
+  }
+  const float ms = m == -INFINITY ? 0.f : m;               // empty splits (lse = -inf) weigh 0
+  float wsum = 0.f;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const float w = fast_exp2((l[u] - ms) * kLog2e);
+    wsum += w;
+    acc.x = fmaf(w, v[u].x, acc.x);
+    acc.y = fmaf(w, v[u].y, acc.y);
+    acc.z = fmaf(w, v[u].z, acc.z);
+    acc.w = fmaf(w, v[u].w, acc.w);
+  }
+  const float inv = wsum > 0.f ? 1.f / wsum : 0.f;
+  const int64_t orow = ((int64_t)b * a.n_max + n) * a.hq + head;
+  const int64_t obase = orow * D + col;
+  store_out(a, obase, acc.x * inv);
+  store_out(a, obase + 1, acc.y * inv);
+  store_out(a, obase + 2, acc.z * inv);
+  store_out(a, obase + 3, acc.w * inv);
+  if (col == 0 && a.lse) a.lse[orow] = wsum > 0.f ? m + logf(wsum) : -INFINITY;
+}
+
 // Status of a launch with no tree nodes at all: every sequence's (empty)
 // tree is valid. A fill kernel rather than a memset, so that the call stays
 // capturable in a graph.
@@ -2213,7 +2296,20 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
   }
 #undef CURE_ATTN
   if (hipGetLastError() != hipSuccess) return CURE_ERR_HIP;
-  if (p.max_splits > 1) {
+  if (p.max_splits > 1 && p.max_splits <= kFewSplits && (int64_t)batch * n_max * hq >= kManyRows) {
+    const int rows = 1024 / d;                          // output rows per workgroup
+    const dim3 mgrid((unsigned)((hq + rows - 1) / rows), (unsigned)n_max, (unsigned)batch);
+#define CURE_MERGE(DD, NN)                                                                                \
+    do {                                                                                                  \
+      if (compact) hipLaunchKernelGGL((attn_merge_few<DD, NN, CompactArgs>), mgrid, dim3(256), 0, st, a); \
+      else hipLaunchKernelGGL((attn_merge_few<DD, NN, Args>), mgrid, dim3(256), 0, st, full);             \
+    } while (0)
+    if (d == 128 && p.max_splits == 2) CURE_MERGE(128, 2);
+    else if (d == 128) CURE_MERGE(128, kFewSplits);
+    else if (p.max_splits == 2) CURE_MERGE(64, 2);
+    else CURE_MERGE(64, kFewSplits);
+#undef CURE_MERGE
+  } else if (p.max_splits > 1) {
     const dim3 mgrid((unsigned)((hq + 3) / 4), (unsigned)n_max, (unsigned)batch);
     const int per_load = 256 / d;                       // splits per merge load
     const int nb = p.max_splits <= 2 * per_load ? 2 : p.max_splits <= 4 * per_load ? 4 : 8;

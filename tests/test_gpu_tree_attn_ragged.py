@@ -70,3 +70,25 @@ def test_host_sizes_only_plan(dtype, group, host):
     torch.cuda.synchronize()
     assert st.tolist() == [pc.CURE_OK] * 4
     check_attn(w, o, lse, *ref)
+
+
+@pytest.mark.parametrize("d,hkv,group,kv_split", [(128, 8, 4, 2), (128, 8, 4, 4), (128, 8, 4, 5), (64, 8, 4, 3),
+                                                  (64, 3, 7, 2), (128, 3, 7, 3)])
+@pytest.mark.parametrize("ragged", [False, True])
+def test_merges_of_many_rows(d, hkv, group, kv_split, ragged):
+    """Launches of at least 16384 output rows and up to four splits take the merge with several rows
+    to a wave; head counts that its workgroups do not divide, stale slots and lone splits among them."""
+    batch, n = 26, 32
+    ctx = [(290 - 9 * i if ragged else 250) for i in range(batch)]
+    nodes = [n - (i % 3 if ragged else 0) for i in range(batch)]
+    nodes[0] = n
+    assert batch * n * hkv * group >= 16384
+    w = general_tree_workload(25, batch, hkv, group, d, nodes, ctx, "nested")
+    sample = [(b, i) for b in (0, 1, 12, 24, 25) for i in (0, 5, nodes[b] - 1)]
+    dev = upload(w)
+    pc.cure_tree_attn(dev["q"] * 100, dev["k"], dev["v"], dev["kv_off"], dev["ctx_len"], dev["n_nodes"],
+                      dev["parent"], w.ctx_len, w.n_nodes, w.scale, kv_split=9)      # other data in the slots
+    o, lse, st = gpu_attn(w, dev, kv_split=kv_split)
+    torch.cuda.synchronize()
+    assert st.tolist() == [pc.CURE_OK] * batch
+    check_attn(w, o, lse, *oracle_attn(w, sample=sample), sample=sample)
