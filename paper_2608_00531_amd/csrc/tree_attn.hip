@@ -17,8 +17,8 @@
 //    16x16x32 bf16 MFMAs, 16 query rows per wave. K/V tiles arrive in LDS by
 //    DMA; V is read back transposed by the LDS transpose-read instruction in
 //    exactly the token order the score MFMA leaves P in registers.
-//  * tree_attn_mfma: the same scheme with 32x32x16 MFMAs and 32 rows per
-//    wave, for head dim 64 beyond 128 rows.
+//  * tree_attn_rg: the same with two or three 16-row groups per wave, for head dim
+//    128 with 257 - 384 rows and head dim 64 beyond 128 rows.
 //  * tree_attn_f32: fp32 on the fp32 matrix instructions, the same scheme with
 //    the rows or the tokens of a block dealt over four waves.
 //  * tree_attn_valu: fp32 or bf16, any supported shape, scale and alignment;
@@ -40,7 +40,6 @@ namespace cure {
 namespace {
 
 constexpr int kTile = 64;            // tokens per K/V tile
-constexpr int kStages = 2;           // K/V tile buffers in the MFMA kernel's LDS ring
 constexpr int kMaxGridY = 65535;     // largest grid y (the split index)
 constexpr int kMinTps = 256;         // tokens per split, at least
 constexpr int kMaxUnits = 512;       // entries of a compact launch's table
@@ -343,26 +342,26 @@ __global__ __launch_bounds__(256) void tree_attn_valu(Args a) {
 }
 
 // ---------------------------------------------------------------------------
-// MFMA split kernel (bf16 in, fp32 accumulate).
+// MFMA split kernels (bf16 in, fp32 accumulate): what they share.
 //
-// Each of the NW waves owns 32 query rows. Per 64-token tile:
-//   S^T = K Q^T  (2 token blocks x D/16 k-steps of 32x32x16 MFMA; lane = query row)
-//   online softmax in the log2 domain, rescaling O only when a row's maximum
-//   rises by more than 2^8 (values then stay below 2^8, safe in bf16 and fp32)
-//   O^T += V^T P^T (D/32 column blocks x 4 k-steps)
+// Per 64-token tile:
+//   S^T = K Q^T, online softmax in the log2 domain, rescaling O only when a row's
+//   maximum rises by more than 2^8 (values then stay below 2^8, safe in bf16 and
+//   fp32), O^T += V^T P^T
 // K and V tiles move HBM -> LDS by DMA (buffer loads that write LDS directly)
-// through a ring of NBUF tile buffers: while one tile is computed, the next
-// NBUF - 1 stream in. Two buffers at head dim 128 leave room for two
-// workgroups (eight waves) per CU; a deeper ring trades those waves for more
-// bytes in flight, and measured slower. The per-sequence buffer resource
-// bounds every read: rows past the sequence end read as zeros, and ring
-// slots past the split's end are filled by reads at an offset past the
-// resource, which touch no memory. LDS rows are 16-byte-chunk XOR-swizzled so
-// that both the K reads (one row per lane) and the transposed V reads (4 rows
-// x 16 columns per 16 lanes, ds_read_b64_tr_b16) spread over the banks.
+// through a ring of tile buffers: while one tile is computed, the next ones stream
+// in. The per-sequence buffer resource bounds every read: rows past the sequence
+// end read as zeros, and ring slots past the split's end are filled by reads at an
+// offset past the resource, which touch no memory. LDS rows are 16-byte-chunk
+// XOR-swizzled so that both the K reads (one row per lane) and the transposed V
+// reads (4 rows x 16 columns per 16 lanes, ds_read_b64_tr_b16) spread over the
+// banks. The DMA is issued from inline assembly on purpose: written through the
+// compiler builtin, every later LDS read of the current tile gets a wait on the
+// next tile's DMA (the compiler cannot tell the buffers apart), which serialises
+// the pipeline. Ordering is explicit instead: each loop iteration starts with
+// s_waitcnt + barrier before any LDS read of the tile it uses.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
@@ -456,300 +455,11 @@ struct TileGeo {
 constexpr int waitcnt_vm(int vm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4); }
 constexpr uint32_t kOobOffset = 0x80000000u;   // past any sequence's buffer resource
 
-template <int D, int NW, int NBUF, class A>
-__global__ __launch_bounds__(64 * NW, NBUF > 2 ? 1 : 2) void tree_attn_mfma(A a) {
-  using G = TileGeo<D>;
-  constexpr int kKSteps = D / 16;                  // MFMA k-steps for Q K^T
-  constexpr int kDBlk = D / 32;                    // 32-column blocks of O^T
-  constexpr int kDmaPerWave = G::kBlocks / NW;     // DMA blocks per wave per tensor
-  // Each loop iteration waits until its tile has landed while the NBUF - 2
-  // tiles issued after it may still be in flight (2 instructions per block).
-  constexpr int kVmWait = waitcnt_vm((NBUF - 2) * 2 * kDmaPerWave);
-  static_assert((NBUF - 2) * 2 * kDmaPerWave < 64, "vmcnt holds 6 bits");
-  static_assert(G::kBlocks % NW == 0, "tile must split evenly across waves");
-
-  __shared__ int s_parent[CURE_MAX_TREE_NODES];
-  __shared__ unsigned long long s_anc[CURE_MAX_TREE_NODES][kAncWords];
-  __shared__ int s_bad;
-  __shared__ __attribute__((aligned(1024))) unsigned char s_k[NBUF][G::kTileBytes];
-  __shared__ __attribute__((aligned(1024))) unsigned char s_v[NBUF][G::kTileBytes];
-
-  const Place at = locate(a);
-  const int b = at.b, hk = at.hk, rb = at.rb, s = at.s;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5, col = lane & 31;
-
-  // This lane's query row, and its query loads: they need only the launch
-  // shape (rows past the sequence's nodes still lie inside q and are zeroed
-  // below), so they go out together with the loads of the sequence's sizes,
-  // as does each thread's parent entry for the tree.
-  const int R = rb * a.rows_per_wg + wave * 32 + col;
-  const bool r_in = R < a.n_max * a.group;
-  bf16x8 qreg[kKSteps];
-  {
-    const int qn = r_in ? R / a.group : 0;
-    const int qh = hk * a.group + (r_in ? R % a.group : 0);
-    const uint16_t* qrow = reinterpret_cast<const uint16_t*>(a.q) +
-                           (((int64_t)b * a.n_max + qn) * a.hq + qh) * D;
-#pragma unroll
-    for (int kk = 0; kk < kKSteps; ++kk) {
-      Pack8 p;
-      p.u = r_in ? *reinterpret_cast<const uint4*>(qrow + kk * 16 + half * 8)
-                 : make_uint4(0, 0, 0, 0);
-      qreg[kk] = p.v;
-    }
-  }
-  const int my_parent = tid < a.n_max ? a.parent[(int64_t)b * a.n_max + tid] : -1;
-
-  // The sequence's sizes and cache offset are independent loads: one round
-  // trip. The empty asm keeps the compiler from sinking the offset's load
-  // below the early exits (a second round trip).
-  const int n_raw = a.n_nodes[b];
-  const int L = a.ctx_len[b];
-  const int64_t off = a.kv_off[b];
-  asm volatile("" : : "s"(n_raw), "s"(L), "s"(off));
-  const int N = min(n_raw, a.n_max);
-  const int T = L + N;
-  const int S = split_count(T, N, a.tps, at.max_splits);
-  const int rows = N * a.group;
-  if (S == 0) {                         // no nodes: nothing to compute; the empty tree is valid
-    report_tree(a, b, true, s == 0 && hk == 0 && rb == 0);
-    return;
-  }
-  if (s >= S || rb * a.rows_per_wg >= rows) return;
-
-  const int begin = s * a.tps;
-  const int end = (s == S - 1) ? T : begin + a.tps;
-
-  // Buffer resources over this sequence's K and V rows (all kv-heads).
-  const uint32_t seq_bytes = (uint32_t)T * (uint32_t)(a.hkv * G::kRowBytes);
-  // Per lane and DMA block: byte offset of the source chunk for tile start 0.
-  uint32_t src_off[kDmaPerWave];
-#pragma unroll
-  for (int j = 0; j < kDmaPerWave; ++j) {
-    const int byte = (wave * kDmaPerWave + j) * 1024 + lane * 16;   // destination in tile
-    const int row = byte / G::kRowBytes;
-    const int pchunk = (byte % G::kRowBytes) >> 4;
-    const int lchunk = pchunk ^ G::swz(row);
-    src_off[j] = (uint32_t)((row * a.hkv + hk) * G::kRowBytes + (lchunk << 4));
-  }
-  const uint32_t tok_bytes = (uint32_t)(a.hkv * G::kRowBytes);
-  // The DMA is issued from inline assembly on purpose: written through the
-  // compiler builtin, every later LDS read of the *current* tile gets a wait on
-  // the *next* tile's DMA (the compiler cannot tell the buffers apart), which
-  // serialises the pipeline. Ordering is explicit instead: each loop iteration
-  // starts with s_waitcnt + barrier before any LDS read of the tile it uses.
-  // A tile at or past the split's end is still issued (at an out-of-range
-  // offset) so that every iteration has the same number of DMAs in flight.
-  const i32x4 rk4 = raw_rsrc(reinterpret_cast<const uint16_t*>(a.k) + off * a.hkv * D, seq_bytes);
-  const i32x4 rv4 = raw_rsrc(reinterpret_cast<const uint16_t*>(a.v) + off * a.hkv * D, seq_bytes);
-  auto dma_tile = [&](int buf, int t0) {
-    const bool live = t0 < end;
-#pragma unroll
-    for (int j = 0; j < kDmaPerWave; ++j) {
-      const uint32_t voff = live ? src_off[j] + (uint32_t)t0 * tok_bytes : kOobOffset;
-      const int blk = (wave * kDmaPerWave + j) * 1024;
-      dma16(lds_addr(&s_k[buf][blk]), voff, rk4);
-      dma16(lds_addr(&s_v[buf][blk]), voff, rv4);
-    }
-  };
-
-  // The first tiles' DMA goes out before anything else this workgroup loads.
-#pragma unroll
-  for (int i = 0; i < NBUF - 1; ++i) dma_tile(i, begin + i * kTile);
-
-  const bool row_ok = R < rows;
-  const int n = row_ok ? R / a.group : 0;
-  const int head = hk * a.group + (row_ok ? R % a.group : 0);
-  const bool wave_active = rb * a.rows_per_wg + wave * 32 < rows;
-
-  // LDS byte offsets used by this lane, independent of the tile.
-  // K rows blk*32 + col, logical chunk 2*kk + half.
-  int k_row_base[2], k_swz[2];
-#pragma unroll
-  for (int blk = 0; blk < 2; ++blk) {
-    const int row = blk * 32 + col;
-    k_row_base[blk] = row * G::kRowBytes;
-    k_swz[blk] = G::swz(row) ^ half;
-  }
-  // V transposed reads: lane j of each 16-lane group reads 8 bytes at row
-  // (4*half + j/4) of a 4-row group, columns 4*(j%4) of a 16-column block.
-  const int j16 = lane & 15, g16 = (lane >> 4) & 1;
-  const int v_row_lane = 4 * half + (j16 >> 2);          // + 16*ks + 8*r
-  const int v_chunk_lane = 2 * g16 + ((j16 & 3) >> 1);   // + 4*i
-  const int v_byte_lane = (j16 & 1) * 8;
-
-  // Only a split that reaches the tree's own rows needs the ancestor masks
-  // (built while the first tile and the queries are in flight). The last
-  // split always does, and it reports the tree's status. With a malformed
-  // tree the other splits still run; the sequence's output is unspecified.
-  if (end > L) {
-    const bool ok = build_tree_loaded(N, my_parent, s_parent, s_anc, &s_bad);
-    report_tree(a, b, ok, s == S - 1 && hk == 0 && rb == 0);
-    if (!ok) {
-      __builtin_amdgcn_s_waitcnt(0);      // no DMA may land after the workgroup ends
-      return;
-    }
-  }
-
-  f32x16 oacc[kDBlk];
-#pragma unroll
-  for (int i = 0; i < kDBlk; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) oacc[i][r] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  const float c = a.scale_log2;
-  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-
-  // Queries and the first tiles have landed. (This also tells the compiler
-  // that no load it issued is pending, so it adds no waits inside the loop.)
-  __builtin_amdgcn_s_waitcnt(0);
-  if (!row_ok) {
-#pragma unroll
-    for (int kk = 0; kk < kKSteps; ++kk) qreg[kk] = bf16x8{};
-  }
-  for (int t0 = begin, buf = 0; t0 < end; t0 += kTile, buf = buf + 1 == NBUF ? 0 : buf + 1) {
-    __builtin_amdgcn_s_waitcnt(kVmWait);  // this wave's DMA into `buf` has landed
-    __syncthreads();                      // everyone's has; the previous buffer is free
-    dma_tile(buf == 0 ? NBUF - 1 : buf - 1, t0 + (NBUF - 1) * kTile);
-    if (!wave_active) continue;
-    const unsigned char* kt = s_k[buf];
-    const unsigned char* vt = s_v[buf];
-
-    // S^T (tokens x query rows), raw dot products; two independent chains.
-    f32x16 sacc[2];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[blk][r] = 0.f;
-    // K operands are read one k-step ahead of the MFMAs that consume them.
-    Pack8 ka[2][2];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
-      ka[0][blk].u = *reinterpret_cast<const uint4*>(kt + k_row_base[blk] + (k_swz[blk] << 4));
-#pragma unroll
-    for (int kk = 0; kk < kKSteps; ++kk) {
-      if (kk + 1 < kKSteps) {
-#pragma unroll
-        for (int blk = 0; blk < 2; ++blk)
-          ka[(kk + 1) & 1][blk].u = *reinterpret_cast<const uint4*>(
-              kt + k_row_base[blk] + (((2 * (kk + 1)) ^ k_swz[blk]) << 4));
-      }
-#pragma unroll
-      for (int blk = 0; blk < 2; ++blk)
-        sacc[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk & 1][blk].v, qreg[kk], sacc[blk], 0, 0, 0);
-    }
-    // Mask the tail, then the tile's row maximum (raw units; the scale is > 0).
-    if (t0 + kTile > L) {
-#pragma unroll
-      for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          sacc[blk][r] += mask_bias(t0 + blk * 32 + 8 * (r >> 2) + 4 * half + (r & 3), L, end, n, s_anc);
-    }
-    // Row maximum: one three-input max per two scores, in two chains.
-    float mb[2] = {-INFINITY, -INFINITY};
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-      for (int r = 0; r < 16; r += 2) mb[blk] = max3_raw(mb[blk], sacc[blk][r], sacc[blk][r + 1]);
-    const float m_tile = max_halves(max3_raw(mb[0], mb[1], mb[1])) * c;
-    // Lazy rescale: move the reference only when the maximum rises by > 2^8.
-    const bool grow = m_tile > m_run + kRescaleLog2;
-    if (__builtin_expect(__ballot(grow) != 0, 0)) {
-      if (grow) {
-        const float alpha = fast_exp2(m_run - m_tile);
-        l_run *= alpha;
-#pragma unroll
-        for (int i = 0; i < kDBlk; ++i)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
-        m_run = m_tile;
-      }
-    }
-    const float nm = m_run == -INFINITY ? 0.f : -m_run;
-    bf16x8 pb[4];
-    float l0 = 0.f, l1 = 0.f;
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        bf16x8 v8;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v8[e] = (__bf16)fast_exp2(fmaf(sacc[blk][8 * j + e], c, nm));
-        pb[blk * 2 + j] = v8;
-        // Row sums of the probabilities as rounded for the MFMA (bf16 pairs).
-#pragma unroll
-        for (int e = 0; e < 8; e += 4) {
-          l0 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{v8[e], v8[e + 1]}, ones, l0, false);
-          l1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{v8[e + 2], v8[e + 3]}, ones, l1, false);
-        }
-      }
-    l_run += l0 + l1;
-
-    // O^T += V^T P^T; the D/32 column blocks are independent chains.
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-#pragma unroll
-      for (int i = 0; i < kDBlk; ++i) {
-        Pack8 va;
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-          const int row = 16 * ks + 8 * r + v_row_lane;
-          const int byte = G::offset(row, 4 * i + v_chunk_lane) + v_byte_lane;
-          va.h[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vt + byte));
-        }
-        oacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va.v, pb[ks], oacc[i], 0, 0, 0);
-      }
-    }
-  }
-
-  __builtin_amdgcn_s_waitcnt(0);          // the ring's trailing DMAs land before exit
-  if (!row_ok) return;
-  const float l_tot = sum_halves(l_run);
-  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  const float lse_nat = l_tot > 0.f ? (m_run + log2f(l_tot)) * kLn2 : -INFINITY;
-  if (S == 1) {
-    const int64_t obase = (((int64_t)b * a.n_max + n) * a.hq + head) * D;
-#pragma unroll
-    for (int i = 0; i < kDBlk; ++i)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int d0 = i * 32 + 8 * g4 + 4 * half;
-        const float x0 = oacc[i][4 * g4] * inv, x1 = oacc[i][4 * g4 + 1] * inv;
-        const float x2 = oacc[i][4 * g4 + 2] * inv, x3 = oacc[i][4 * g4 + 3] * inv;
-        if (a.out_bf16) {
-          uint2 pk;
-          pk.x = pack_bf16x2(x0, x1);
-          pk.y = pack_bf16x2(x2, x3);
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.o) + obase + d0) = pk;
-        } else {
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.o) + obase + d0) =
-              make_float4(x0, x1, x2, x3);
-        }
-      }
-    if (half == 0 && a.lse) a.lse[((int64_t)b * a.n_max + n) * a.hq + head] = lse_nat;
-  } else {
-    const int64_t pi = part_index(a, b, head, n, s);
-#pragma unroll
-    for (int i = 0; i < kDBlk; ++i)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int d0 = i * 32 + 8 * g4 + 4 * half;
-        *reinterpret_cast<float4*>(a.part_o + pi * D + d0) =
-            make_float4(oacc[i][4 * g4] * inv, oacc[i][4 * g4 + 1] * inv,
-                        oacc[i][4 * g4 + 2] * inv, oacc[i][4 * g4 + 3] * inv);
-      }
-    if (half == 0) a.part_lse[pi] = lse_nat;
-  }
-}
-
 // ---------------------------------------------------------------------------
 // MFMA split kernel with 16 query rows per wave (v_mfma_f32_16x16x32_bf16).
 //
-// Same tile stream, LDS layout, tree mask and lazily rescaled online softmax
-// as the 32-row kernel above (here a tile's row maxima are reduced only when a
-// rescale could be due), at half the registers per wave, so that two 8-wave
+// A tile's row maxima are reduced only when a rescale could be due. Few registers
+// per wave, so that two 8-wave
 // workgroups (four waves per SIMD) share a CU, and row blocks of up to 256
 // rows fit one 16-wave workgroup with the rows spread evenly over the SIMDs.
 // Wider trees take several row blocks of equal size (a multiple of 16 rows).
@@ -1942,6 +1652,7 @@ enum class Path { kValu, kF32, kBf16 };   // kernel family: vector ALU, fp32 or 
 struct Plan {
   Path path;
   bool rows16;        // MFMA kernel with 16 query rows per wave
+  bool rows64;        // head dim 64 beyond 128 rows: tree_attn_rg with two or three row groups
   bool rows48;        // MFMA kernel with three 16-row groups per wave (tree_attn_rg)
   int nw;             // waves per workgroup (MFMA kernel)
   int rows_per_wg;
@@ -1956,24 +1667,7 @@ struct Plan {
 // tile; planned for 257 - 384 rows.
 constexpr int kRg3Waves = 8;
 constexpr int kRg3Rows = kRg3Waves * 48;
-
-// MFMA workgroups one CU holds at once: bounded by LDS (the K/V ring plus the
-// tree masks) and by registers (about 220 VGPRs per lane at head dim 128, so
-// two waves per SIMD; about 120 at head dim 64, four waves per SIMD).
-int mfma_wgs_per_cu(int d, int nw, bool rows16, bool rows48) {
-  if (rows48) return 1;
-  constexpr int kLdsPerCu = 160 * 1024;
-  const int stages = rows16 ? 2 : kStages;
-  const int lds = 2 * stages * kTile * d * 2 +
-                  CURE_MAX_TREE_NODES * (4 + kAncWords * 8) + 64;
-  const int by_lds = kLdsPerCu / lds;
-  // 16-row waves hold about half the registers: four waves per SIMD. The
-  // 8-wave 16-row kernel is planned at one workgroup per CU all the same:
-  // the longer splits halve the partial rows the merge reads, and a second
-  // workgroup per CU measured no faster.
-  const int by_regs = rows16 ? 8 / nw : (d == 128 ? 8 : 16) / nw;
-  return std::max(1, std::min(by_lds, by_regs));
-}
+constexpr int kManyTokens64 = 800;   // tokens per CU, head dim 64 beyond 128 rows (make_plan)
 
 Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
                const int32_t* host_ctx_len, const int32_t* host_n_nodes, int32_t kv_split,
@@ -1989,9 +1683,11 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
   // context x 8 sequences: 320 rows 126 µs against 144 for two 160-row
   // blocks of the 16-row kernel, 352 rows 139 against 151; at 224 and 256
   // rows the 16-row kernel's single block is ahead (103 vs 106, 109 vs 113).
-  // Head dim 64: the 16-row kernel up to 128 rows, else the 32-row kernel.
+  // Head dim 64: the 16-row kernel up to 128 rows, else two or three row groups
+  // per wave.
   p.rows48 = mfma && d == 128 && rows > 256 && rows <= kRg3Rows;
-  p.rows16 = mfma && !p.rows48 && (d == 128 || rows <= 128);
+  p.rows64 = mfma && d == 64 && rows > 128;
+  p.rows16 = mfma && !p.rows48 && !p.rows64;
   if (p.rows48) {
     // 257 - 384 rows: one block of eight waves of two or three 16-row groups,
     // so each K/V tile is streamed once per kv-head (two 16-row blocks would
@@ -2006,11 +1702,26 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
     p.row_blocks = (rows + 255) / 256;
     p.rows_per_wg = ((rows + p.row_blocks - 1) / p.row_blocks + 15) / 16 * 16;
     p.nw = p.rows_per_wg > 128 ? 16 : 8;
+  } else if (p.rows64) {
+    // Balanced blocks of at most 256 rows on 8 waves of two row groups, one
+    // workgroup per CU, or, once a CU has many tokens to take, of at most 192
+    // rows on 4 waves of three, two workgroups per CU: half the barriers' reach
+    // and a third fewer LDS reads per row, at a longer start. Per call (two
+    // groups, three, and the earlier 32-row MFMA kernel), 8 ragged sequences of
+    // 1k - 4k tokens: 192 rows 27.7, 29.5, 30.6 us, 384 rows 31.6, 33.5, 36.2;
+    // 8 of 8k tokens, 320 rows 81.8, 71.5, 87.6; 16 of 8k, 192 rows 86.8, 80.3,
+    // 86.9; 8 ragged, 640 rows 43.6, 42.2, 43.1. The line lies between 625 and
+    // 940 tokens per CU.
+    int64_t tokens = 0;
+    for (int b = 0; b < batch; ++b)
+      if (host_n_nodes[b] > 0) tokens += (int64_t)host_ctx_len[b] + host_n_nodes[b];
+    const bool many = tokens * hkv * ((rows + 255) / 256) >= kManyTokens64 * (int64_t)device_cu_count();
+    const int most = many ? 192 : 256;
+    p.row_blocks = (rows + most - 1) / most;
+    p.rows_per_wg = ((rows + p.row_blocks - 1) / p.row_blocks + 15) / 16 * 16;
+    p.nw = many ? 4 : 8;
   } else {
-    if (mfma) {
-      p.nw = 8;
-      p.rows_per_wg = 32 * p.nw;
-    } else if (path == Path::kF32) {
+    if (path == Path::kF32) {
       // Four waves over 32 rows, two to a row group (F32Geo's WT = 2): the
       // vector-ALU kernel's blocks, and with two workgroups per CU its splits,
       // so no call needs more workspace. Up to 16 rows share the tokens four ways.
@@ -2042,10 +1753,13 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
     }
     return c * hkv * p.row_blocks;
   };
-  const int wgs_per_cu = mfma ? mfma_wgs_per_cu(d, p.nw, p.rows16, p.rows48)
-                         : path == Path::kF32 && d == 128 && p.rows_per_wg == 16
-                             ? F32Geo<128, 4>::kWgsPerCu
-                             : 2;
+  // Workgroups planned per CU. Two 8-wave 16-row workgroups fit one, but the
+  // longer splits of one halve the partial rows the merge reads, and a second
+  // workgroup measured no faster.
+  int wgs_per_cu = 2;
+  if (p.rows16 || p.rows48) wgs_per_cu = 1;
+  else if (p.rows64) wgs_per_cu = p.nw == 4 ? 2 : 1;
+  else if (path == Path::kF32 && d == 128 && p.rows_per_wg == 16) wgs_per_cu = F32Geo<128, 4>::kWgsPerCu;
   const int64_t slots = (int64_t)wgs_per_cu * device_cu_count();
   // The shortest split (at least kMinTps tokens) whose workgroups are all
   // resident at once, so no workgroup waits for a second round. A batch with
@@ -2280,8 +1994,9 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
     if (d == 128 && p.nw == 8) CURE_ATTN(512, tree_attn_m16, 128, 8);
     else if (d == 128) CURE_ATTN(1024, tree_attn_m16, 128, 16);
     else CURE_ATTN(512, tree_attn_m16, 64, 8);
-  } else if (mfma) {
-    CURE_ATTN(512, tree_attn_mfma, 64, 8, kStages);
+  } else if (p.rows64) {
+    if (p.nw == 4) CURE_ATTN(256, tree_attn_rg, 64, 4, 3, 2, 4, 1, 2);
+    else CURE_ATTN(512, tree_attn_rg, 64, 8, 2, 2, 8, 2, 3);
   } else if (path == Path::kF32) {
     if (d == 128 && p.rows_per_wg == 16) CURE_ATTN(256, tree_attn_f32, 128, 4);
     else if (d == 128) CURE_ATTN(256, tree_attn_f32, 128, 2);
