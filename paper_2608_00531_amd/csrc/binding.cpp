@@ -144,14 +144,16 @@ struct Outputs {
 CURE_KEYS(X)
 #undef X
 
-// Calls of the C ABI release the GIL, as a foreign call does.
+// Calls of the C ABI release the GIL, as a foreign call does. f touches no tensor
+// and no Python object: its pointers are taken before (data_ptr() throws for a
+// tensor without storage, as under vmap).
 template <typename F>
 cure_status unlocked(F&& f) {
-  cure_status st;
-  Py_BEGIN_ALLOW_THREADS
-  st = f();
-  Py_END_ALLOW_THREADS
-  return st;
+  struct Released {
+    PyThreadState* state = PyEval_SaveThread();
+    ~Released() { PyEval_RestoreThread(state); }
+  } released;
+  return f();
 }
 
 void need_args(Py_ssize_t got, Py_ssize_t want) {
@@ -224,6 +226,9 @@ PyObject* py_margins(PyObject*, PyObject* const* args, Py_ssize_t n) {
     void* s = stream_of(x);
     const int32_t b = (int32_t)batch, r = (int32_t)rows, v = (int32_t)vocab;
     const void* lp = x.data_ptr();
+    const int32_t* tp[4] = {};           // parent, token, root_tgt, n_nodes
+    if (accept)
+      for (int i = 0; i < 4; ++i) tp[i] = i32_ptr(tree[i]);
     const int64_t ld = x.stride(1);
     if (noalloc) {
       check(unlocked([&] {
@@ -236,9 +241,8 @@ PyObject* py_margins(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (accept)
       check(unlocked([&] {
               return cure_margins_accept(lp, dtype, b, r, v, ld, v1, i1, v2, i2, lse, margin, chain, tau,
-                                         budget, depth, pos, cnt, i32_ptr(tree[0]), i32_ptr(tree[1]),
-                                         i32_ptr(tree[2]), i32_ptr(tree[3]), acc_len, path, best, bonus,
-                                         resync, ws.ptr, ws.bytes, s);
+                                         budget, depth, pos, cnt, tp[0], tp[1], tp[2], tp[3], acc_len, path,
+                                         best, bonus, resync, ws.ptr, ws.bytes, s);
             }), "cure_margins_accept");
     else
       check(unlocked([&] {
@@ -317,13 +321,16 @@ PyObject* py_tree_attn(PyObject*, PyObject* const* args, Py_ssize_t n) {
     void* s = stream_of(q);
     const Workspace ws = workspace(kAttn, q, s, cure_tree_attn_workspace_size(
         (int32_t)batch, (int32_t)hq, (int32_t)hkv, (int32_t)d, (int32_t)n_max, hc.data(), hn.data(), split));
+    const void *qp = q.data_ptr(), *kp = k.data_ptr(), *vp = v.data_ptr();
+    void* op = o.data_ptr();
+    float* lsep = with_lse ? static_cast<float*>(lse.data_ptr()) : nullptr;
+    const int64_t* offp = static_cast<const int64_t*>(kv_off.data_ptr());
+    const int32_t *cp = i32_ptr(ctx), *np = i32_ptr(nn), *pp = i32_ptr(par);
+    int32_t* stp = static_cast<int32_t*>(status.data_ptr());
     check(unlocked([&] {
-            return cure_tree_attn(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                                  with_lse ? static_cast<float*>(lse.data_ptr()) : nullptr, dt, odt,
-                                  (int32_t)batch, (int32_t)hq, (int32_t)hkv, (int32_t)d, scale,
-                                  static_cast<const int64_t*>(kv_off.data_ptr()), i32_ptr(ctx), i32_ptr(nn),
-                                  i32_ptr(par), (int32_t)n_max, hc.data(), hn.data(), split, flags,
-                                  static_cast<int32_t*>(status.data_ptr()), ws.ptr, ws.bytes, s);
+            return cure_tree_attn(qp, kp, vp, op, lsep, dt, odt, (int32_t)batch, (int32_t)hq, (int32_t)hkv,
+                                  (int32_t)d, scale, offp, cp, np, pp, (int32_t)n_max, hc.data(), hn.data(),
+                                  split, flags, stp, ws.ptr, ws.bytes, s);
           }), "cure_tree_attn");
     PyObject* r = PyTuple_New(3);
     if (!r) throw PyError{};
@@ -359,9 +366,11 @@ PyObject* py_accept(PyObject*, PyObject* const* args, Py_ssize_t n) {
     int32_t* bonus = out.add<int32_t>(k_bonus, empty({batch}, at::kInt, t[0]));
     int32_t* resync = out.add<int32_t>(k_resync, empty({batch}, at::kInt, t[0]));
     void* s = stream_of(t[0]);
+    const int32_t* p[5];
+    for (int i = 0; i < 5; ++i) p[i] = i32_ptr(t[i]);
     check(unlocked([&] {
-            return cure_accept(i32_ptr(t[0]), i32_ptr(t[1]), i32_ptr(t[2]), i32_ptr(t[3]), i32_ptr(t[4]),
-                               chain, (int32_t)batch, (int32_t)n_max, len, path, best, bonus, resync, s);
+            return cure_accept(p[0], p[1], p[2], p[3], p[4], chain, (int32_t)batch, (int32_t)n_max, len, path,
+                               best, bonus, resync, s);
           }), "cure_accept");
     return out.take();
   });
@@ -416,12 +425,15 @@ PyObject* py_repair_tree(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const Workspace ws = workspace(kRepair, x, s, cure_repair_tree_workspace_size(
         (int32_t)batch, (int32_t)chain, (int32_t)vocab, budget, depth));
     const int32_t dtype = dtype_code(x);
+    const void* lp = x.data_ptr();
+    const int64_t ld = x.stride(1);
+    const float* mp = static_cast<const float*>(t[0].data_ptr());
+    const int32_t *pos = i32_ptr(t[1]), *cnt = i32_ptr(t[2]), *tok = i32_ptr(t[3]);
+    const int32_t* suffix = use_suffix ? i32_ptr(t[4]) : nullptr;
     check(unlocked([&] {
-            return cure_repair_tree(x.data_ptr(), dtype, (int32_t)batch, (int32_t)rows, (int32_t)vocab,
-                                    x.stride(1), static_cast<const float*>(t[0].data_ptr()), i32_ptr(t[1]),
-                                    i32_ptr(t[2]), i32_ptr(t[3]), (int32_t)chain, budget, depth, scale, b_min,
-                                    b_max, use_suffix ? i32_ptr(t[4]) : nullptr, (int32_t)n_max, parent,
-                                    token, nodes, branches, ws.ptr, ws.bytes, s);
+            return cure_repair_tree(lp, dtype, (int32_t)batch, (int32_t)rows, (int32_t)vocab, ld, mp, pos, cnt,
+                                    tok, (int32_t)chain, budget, depth, scale, b_min, b_max, suffix,
+                                    (int32_t)n_max, parent, token, nodes, branches, ws.ptr, ws.bytes, s);
           }), "cure_repair_tree");
     return out.take();
   });
@@ -465,11 +477,14 @@ PyObject* py_commit(PyObject*, PyObject* const* args, Py_ssize_t n) {
     for (int i = 2; i < 9; ++i) t[i] = t[i].contiguous();
     const int32_t dtype = dtype_code(k);
     void* s = stream_of(k);
+    void *kp = k.data_ptr(), *vp = v.data_ptr();
+    const int64_t* offp = static_cast<const int64_t*>(t[2].data_ptr());
+    const int32_t* p[6];                 // ctx_len, n_nodes, path, acc_len, token, bonus
+    for (int i = 0; i < 6; ++i) p[i] = i32_ptr(t[3 + i]);
     check(unlocked([&] {
-            return cure_commit(k.data_ptr(), v.data_ptr(), dtype, (int32_t)layers, stride, (int32_t)hkv,
-                               (int32_t)d, (int32_t)batch, static_cast<const int64_t*>(t[2].data_ptr()),
-                               i32_ptr(t[3]), i32_ptr(t[4]), i32_ptr(t[5]), i32_ptr(t[6]), i32_ptr(t[7]),
-                               i32_ptr(t[8]), chain, (int32_t)n_max, ctx, emit, cnt, replay, status, s);
+            return cure_commit(kp, vp, dtype, (int32_t)layers, stride, (int32_t)hkv, (int32_t)d, (int32_t)batch,
+                               offp, p[0], p[1], p[2], p[3], p[4], p[5], chain, (int32_t)n_max, ctx, emit, cnt,
+                               replay, status, s);
           }), "cure_commit");
     return out.take();
   });

@@ -1,0 +1,73 @@
+"""The Python binding's use of the interpreter lock, on the CPU.
+
+A stub (binding_stub.cpp) stands in for the stream look-up, and fake tensors for the
+GPU's. Each check runs in a process of its own, since a fault here ends the process.
+"""
+
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+import torch
+from torch.utils import cpp_extension
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PRELUDE = """
+import ctypes, sys, warnings
+warnings.simplefilter("ignore")                      # fake tensors' pointers
+stub = ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)  # before the binding's own libraries
+import torch
+from torch._subclasses import FakeTensorMode
+import paper_2608_00531_amd as pc
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("stub") / "stub.so")
+    cmd = ["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+    for path in cpp_extension.include_paths("cuda"):
+        cmd += ["-isystem", path]
+    res = subprocess.run(cmd + [os.path.join(HERE, "binding_stub.cpp"), "-o", out], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+    return out
+
+
+def child(stub, code, *args):
+    res = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(code), stub, *args],
+                         cwd=os.path.dirname(HERE), capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout + res.stderr
+    return res.stdout.split()
+
+
+@pytest.mark.parametrize("name", ["margins", "margins_noalloc", "margins_accept", "margins_accept_tree",
+                                  "tree_attn", "accept", "repair_tree", "commit"])
+def test_tensors_without_storage_raise(stub, name):
+    """A tensor under vmap has no data pointer: every call says so and the process lives."""
+    out = child(stub, """
+        with FakeTensorMode():
+            f = lambda *s: torch.zeros(3, *s, device="cuda")
+            i = lambda *s: torch.zeros(3, *s, dtype=torch.int32, device="cuda")
+            x, n, t, m = f(2, 4, 16), i(2), i(2, 4), f(2, 4)
+            q, k, off = f(2, 4, 2, 64), f(40, 2, 64), torch.zeros(3, 2, dtype=torch.int64, device="cuda")
+            fn, args = {
+                "margins": (pc.cure_margins, [x]),
+                "margins_noalloc": (pc.cure_margins_noalloc, [x]),
+                "margins_accept": (lambda x, t, n: pc.cure_margins_accept(x, t, t, n, n, 4), [x, t, n]),
+                "margins_accept_tree": (lambda t, n: pc.cure_margins_accept(x[0], t, t, n, n, 4), [t, n]),
+                "tree_attn": (lambda q, k, off, n, t: pc.cure_tree_attn(q, k, k, off, n, n, t, [8, 8], [4, 4], 1.0),
+                              [q, k, off, n, t]),
+                "accept": (lambda t, n: pc.cure_accept(t, t, t, n, n, 4), [t, n]),
+                "repair_tree": (lambda x, m, t, n: pc.cure_repair_tree(x, m, t, n, t, 4, 2, 1.0), [x, m, t, n]),
+                "commit": (lambda k, off, n, t: pc.cure_commit(k, k, off, n, n, t, n, t, n, 4), [k, off, n, t]),
+            }[sys.argv[2]]
+            try:
+                torch.vmap(fn)(*args)
+            except RuntimeError as e:
+                print("refused" if "data pointer" in str(e) else e)
+        """, name)
+    assert out == ["refused"]
