@@ -793,7 +793,13 @@ void tree_attn_rg(A a) {
   constexpr int kDBlk = D / 16;                    // 16-column blocks of O^T
   constexpr int kDmaBlocks = G::kBlocks / NDMA;    // DMA blocks per DMA wave per tensor
   // The tile's 64 tokens are taken in HT steps of online softmax, each of
-  // kTB 16-token blocks (scores) and kPV 32-token k-steps (P V).
+  // kTB 16-token blocks (scores) and kPV 32-token k-steps (P V). Head dim 128
+  // takes two, for its registers. Head dim 64 takes one, as the 16-row kernel: a
+  // row's probabilities are rounded to bf16 against the maximum of the first
+  // step, so the more tokens that covers, the more often the largest one is
+  // exactly 1. In two steps the error against 64 bits was 1.2 % larger (192 rows,
+  // 8 sequences of 1k - 4k tokens: 2.323e-3 of the output and 2.295e-3) and the
+  // calls were 0 - 10 % slower.
   constexpr int kTB = 4 / HT;
   constexpr int kPV = 2 / HT;
   constexpr int kKFrags = kTB * kKSteps;           // K operand fragments per step
@@ -1667,7 +1673,8 @@ struct Plan {
 // tile; planned for 257 - 384 rows.
 constexpr int kRg3Waves = 8;
 constexpr int kRg3Rows = kRg3Waves * 48;
-constexpr int kManyTokens64 = 800;   // tokens per CU, head dim 64 beyond 128 rows (make_plan)
+// Head dim 64 beyond 128 rows: the most rows of a four-wave workgroup.
+constexpr int kRg64Rows4 = 4 * 48;
 
 Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
                const int32_t* host_ctx_len, const int32_t* host_n_nodes, int32_t kv_split,
@@ -1688,6 +1695,11 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
   p.rows48 = mfma && d == 128 && rows > 256 && rows <= kRg3Rows;
   p.rows64 = mfma && d == 64 && rows > 128;
   p.rows16 = mfma && !p.rows48 && !p.rows64;
+  // Row blocks of at most `most` rows, balanced, in multiples of 16.
+  const auto balance_rows = [&](int most) {
+    p.row_blocks = (rows + most - 1) / most;
+    p.rows_per_wg = ((rows + p.row_blocks - 1) / p.row_blocks + 15) / 16 * 16;
+  };
   if (p.rows48) {
     // 257 - 384 rows: one block of eight waves of two or three 16-row groups,
     // so each K/V tile is streamed once per kv-head (two 16-row blocks would
@@ -1698,28 +1710,11 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
     p.rows_per_wg = (rows + 15) / 16 * 16;
     p.nw = kRg3Waves;
   } else if (p.rows16) {
-    // Row blocks of at most 256 rows, balanced, in multiples of 16.
-    p.row_blocks = (rows + 255) / 256;
-    p.rows_per_wg = ((rows + p.row_blocks - 1) / p.row_blocks + 15) / 16 * 16;
+    balance_rows(256);
     p.nw = p.rows_per_wg > 128 ? 16 : 8;
   } else if (p.rows64) {
-    // Balanced blocks of at most 256 rows on 8 waves of two row groups, one
-    // workgroup per CU, or, once a CU has many tokens to take, of at most 192
-    // rows on 4 waves of three, two workgroups per CU: half the barriers' reach
-    // and a third fewer LDS reads per row, at a longer start. Per call (two
-    // groups, three, and the earlier 32-row MFMA kernel), 8 ragged sequences of
-    // 1k - 4k tokens: 192 rows 27.7, 29.5, 30.6 us, 384 rows 31.6, 33.5, 36.2;
-    // 8 of 8k tokens, 320 rows 81.8, 71.5, 87.6; 16 of 8k, 192 rows 86.8, 80.3,
-    // 86.9; 8 ragged, 640 rows 43.6, 42.2, 43.1. The line lies between 625 and
-    // 940 tokens per CU.
-    int64_t tokens = 0;
-    for (int b = 0; b < batch; ++b)
-      if (host_n_nodes[b] > 0) tokens += (int64_t)host_ctx_len[b] + host_n_nodes[b];
-    const bool many = tokens * hkv * ((rows + 255) / 256) >= kManyTokens64 * (int64_t)device_cu_count();
-    const int most = many ? 192 : 256;
-    p.row_blocks = (rows + most - 1) / most;
-    p.rows_per_wg = ((rows + p.row_blocks - 1) / p.row_blocks + 15) / 16 * 16;
-    p.nw = many ? 4 : 8;
+    // Blocks of at most 256 rows at first; the waves come with the splits, below.
+    balance_rows(256);
   } else {
     if (path == Path::kF32) {
       // Four waves over 32 rows, two to a row group (F32Geo's WT = 2): the
@@ -1758,9 +1753,9 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
   // workgroup measured no faster.
   int wgs_per_cu = 2;
   if (p.rows16 || p.rows48) wgs_per_cu = 1;
-  else if (p.rows64) wgs_per_cu = p.nw == 4 ? 2 : 1;
   else if (path == Path::kF32 && d == 128 && p.rows_per_wg == 16) wgs_per_cu = F32Geo<128, 4>::kWgsPerCu;
-  const int64_t slots = (int64_t)wgs_per_cu * device_cu_count();
+  const int64_t cus = device_cu_count();
+  int64_t slots = wgs_per_cu * cus;
   // The shortest split (at least kMinTps tokens) whose workgroups are all
   // resident at once, so no workgroup waits for a second round. A batch with
   // more sequence x head pairs than that gets a single split per sequence.
@@ -1795,6 +1790,34 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
     tps = make_plan(batch, hq, hkv, d, n_max, host_ctx_len, host_n_nodes, 0, Path::kBf16).tps;
   } else {
     tps = shortest_resident_split();
+    // Head dim 64 beyond 128 rows: tree_attn_rg with four waves of three row
+    // groups, two workgroups per CU, or with eight waves of two, one per CU. Rows
+    // that balance to blocks of at most 192 keep the split length for two per CU
+    // either way, and eight waves take them when one per CU holds the launch:
+    // with equal splits they start faster (4 sequences of 0.5k - 2k tokens, 192
+    // rows: 17.6 us a call against 19.2), and two four-wave workgroups fill a CU
+    // better (16 of 8k: 79.3 against 84.5). Other rows are cut into blocks of at
+    // most 256 for eight waves or of at most 192 for four, whichever gives the
+    // busiest SIMD fewer row groups x tiles: 16 sequences of 8k tokens, 512 rows
+    // 97 us in two blocks of 256 and 121 in three of 176 (half of the second
+    // round of CUs idle), 640 rows 158 in three of 224 and 126 in four of 160; 8
+    // of 8k, 256 rows 37 and 42.
+    if (p.rows64 && p.rows_per_wg > kRg64Rows4) {
+      const auto cost = [&]() {
+        const int64_t wgs = workgroups(tps), per_cu = std::min((wgs + cus - 1) / cus, slots / cus);
+        return (wgs + slots - 1) / slots * (tps / kTile) * per_cu * ((p.rows_per_wg / 16 + 3) / 4);
+      };
+      balance_rows(kRg64Rows4);
+      tps = shortest_resident_split();
+      const int64_t cost4 = cost(), tps4 = tps;
+      balance_rows(256);
+      slots = cus;
+      tps = shortest_resident_split();
+      if (cost4 < cost()) {
+        balance_rows(kRg64Rows4);
+        tps = tps4;
+      }
+    }
     // A small launch (even the shortest splits leave most CUs idle, as for one
     // sequence) cuts the 16-row kernel's rows into more blocks, of at least 32
     // rows: the blocks of one kv-head and split are hkv workgroup ids apart,
@@ -1811,6 +1834,7 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
       }
     }
   }
+  if (p.rows64) p.nw = p.rows_per_wg > kRg64Rows4 || workgroups(tps) <= cus ? 8 : 4;
   // Splits index the grid's y dimension (at most kMaxGridY).
   tps = std::max<int64_t>(tps, round_tile((t_max + kMaxGridY - 1) / kMaxGridY));
   p.tps = (int)std::min<int64_t>(tps, INT32_MAX / 2);
@@ -1996,7 +2020,7 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
     else CURE_ATTN(512, tree_attn_m16, 64, 8);
   } else if (p.rows64) {
     if (p.nw == 4) CURE_ATTN(256, tree_attn_rg, 64, 4, 3, 2, 4, 1, 2);
-    else CURE_ATTN(512, tree_attn_rg, 64, 8, 2, 2, 8, 2, 3);
+    else CURE_ATTN(512, tree_attn_rg, 64, 8, 2, 2, 8, 1, 3);
   } else if (path == Path::kF32) {
     if (d == 128 && p.rows_per_wg == 16) CURE_ATTN(256, tree_attn_f32, 128, 4);
     else if (d == 128) CURE_ATTN(256, tree_attn_f32, 128, 2);
