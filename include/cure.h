@@ -42,7 +42,9 @@
  *    needed and the pointer may be NULL). A workspace holds scratch data only
  *    while the call's kernels run: it needs no initialisation and may be reused
  *    by any later call on the same stream. Two calls whose work may overlap on
- *    the GPU must not share a workspace.
+ *    the GPU must not share a workspace, and neither must two calls that threads
+ *    make on one stream at the same time: a call enqueues several kernels, and
+ *    the other's could come between them.
  *  - bf16 values are raw IEEE bfloat16 bit patterns (uint16 storage).
  */
 #ifndef CURE_H
@@ -156,7 +158,8 @@ cure_status cure_margins_accept(const void* logits, int32_t dtype, int32_t batch
  * CURE_ERR_HIP when the array cannot be found on the current device, else as
  * cure_margins. Every call on one GPU shares that GPU's array and leaves its
  * contents behind: calls whose work may overlap on the GPU (different streams
- * without ordering between them) race and must not be issued. */
+ * without ordering between them) race and must not be issued, nor may two
+ * threads be inside this call at the same time. */
 size_t cure_margins_noalloc_scratch_bytes(void);
 
 cure_status cure_margins_noalloc(const void* logits, int32_t dtype, int32_t batch,

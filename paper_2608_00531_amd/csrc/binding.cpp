@@ -17,6 +17,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <map>
+#include <mutex>
 #include <tuple>
 #include <vector>
 
@@ -92,24 +93,35 @@ at::Tensor empty(c10::IntArrayRef shape, at::ScalarType type, const at::Tensor& 
 }
 
 // Zero-filled device workspace, reused per (kind, device, stream) and grown when
-// a call needs more. Guarded by the GIL; lives as long as the process. A call
-// holds the tensor itself until its kernels are enqueued, in case another
-// thread on the same stream has it replaced by a larger one meanwhile.
+// a call needs more; lives as long as the process. The table is guarded by the
+// GIL. A call holds the tensor itself until its kernels are enqueued, in case
+// another thread on the same stream has it replaced by a larger one meanwhile,
+// and `enqueue` while it enqueues them: its kernels pass data through the
+// workspace, so another call's must not come between them on the stream.
 struct Workspace {
   void* ptr;
   size_t bytes;
   at::Tensor held;
+  std::mutex* enqueue;
 };
 enum Kind { kMargins, kAttn, kRepair };
 Workspace workspace(Kind kind, const at::Tensor& like, void* stream, size_t bytes) {
-  if (bytes == 0) return {nullptr, 0, {}};
-  static auto* kept = new std::map<std::tuple<int, int, void*>, at::Tensor>;
-  at::Tensor& ws = (*kept)[{(int)kind, (int)like.device().index(), stream}];
+  if (bytes == 0) return {nullptr, 0, {}, nullptr};
+  struct Slot {
+    at::Tensor buffer;
+    std::mutex enqueue;
+  };
+  static auto* kept = new std::map<std::tuple<int, int, void*>, Slot>;
+  Slot& slot = (*kept)[{(int)kind, (int)like.device().index(), stream}];
+  at::Tensor& ws = slot.buffer;
   if (!ws.defined() || (size_t)ws.numel() < bytes)
     ws = at::zeros({(int64_t)std::max<size_t>(bytes, 256)},
                    at::TensorOptions().dtype(at::kByte).device(like.device()));
-  return {ws.data_ptr(), (size_t)ws.numel(), ws};
+  return {ws.data_ptr(), (size_t)ws.numel(), ws, &slot.enqueue};
 }
+// The same for the scratch array inside the library that cure_margins_noalloc
+// calls share.
+std::mutex g_noalloc;
 
 // The outputs of a call, in the order they are returned in.
 struct Outputs {
@@ -146,13 +158,16 @@ CURE_KEYS(X)
 
 // Calls of the C ABI release the GIL, as a foreign call does. f touches no tensor
 // and no Python object: its pointers are taken before (data_ptr() throws for a
-// tensor without storage, as under vmap).
+// tensor without storage, as under vmap). `order`, if any, is held during the call;
+// it is only ever waited for without the GIL.
 template <typename F>
-cure_status unlocked(F&& f) {
+cure_status unlocked(F&& f, std::mutex* order = nullptr) {
   struct Released {
     PyThreadState* state = PyEval_SaveThread();
     ~Released() { PyEval_RestoreThread(state); }
   } released;
+  std::unique_lock<std::mutex> held;
+  if (order) held = std::unique_lock<std::mutex>(*order);
   return f();
 }
 
@@ -234,7 +249,7 @@ PyObject* py_margins(PyObject*, PyObject* const* args, Py_ssize_t n) {
       check(unlocked([&] {
               return cure_margins_noalloc(lp, dtype, b, r, v, ld, v1, i1, v2, i2, lse, margin, chain, tau,
                                           budget, depth, pos, cnt, s);
-            }), "cure_margins_noalloc");
+            }, &g_noalloc), "cure_margins_noalloc");
       return out.take();
     }
     const Workspace ws = workspace(kMargins, x, s, cure_margins_workspace_size(b, r, v));
@@ -243,12 +258,12 @@ PyObject* py_margins(PyObject*, PyObject* const* args, Py_ssize_t n) {
               return cure_margins_accept(lp, dtype, b, r, v, ld, v1, i1, v2, i2, lse, margin, chain, tau,
                                          budget, depth, pos, cnt, tp[0], tp[1], tp[2], tp[3], acc_len, path,
                                          best, bonus, resync, ws.ptr, ws.bytes, s);
-            }), "cure_margins_accept");
+            }, ws.enqueue), "cure_margins_accept");
     else
       check(unlocked([&] {
               return cure_margins(lp, dtype, b, r, v, ld, v1, i1, v2, i2, lse, margin, chain, tau, budget,
                                   depth, pos, cnt, ws.ptr, ws.bytes, s);
-            }), "cure_margins");
+            }, ws.enqueue), "cure_margins");
     return out.take();
   });
 }
@@ -331,7 +346,7 @@ PyObject* py_tree_attn(PyObject*, PyObject* const* args, Py_ssize_t n) {
             return cure_tree_attn(qp, kp, vp, op, lsep, dt, odt, (int32_t)batch, (int32_t)hq, (int32_t)hkv,
                                   (int32_t)d, scale, offp, cp, np, pp, (int32_t)n_max, hc.data(), hn.data(),
                                   split, flags, stp, ws.ptr, ws.bytes, s);
-          }), "cure_tree_attn");
+          }, ws.enqueue), "cure_tree_attn");
     PyObject* r = PyTuple_New(3);
     if (!r) throw PyError{};
     PyTuple_SET_ITEM(r, 0, THPVariable_Wrap(o));
@@ -434,7 +449,7 @@ PyObject* py_repair_tree(PyObject*, PyObject* const* args, Py_ssize_t n) {
             return cure_repair_tree(lp, dtype, (int32_t)batch, (int32_t)rows, (int32_t)vocab, ld, mp, pos, cnt,
                                     tok, (int32_t)chain, budget, depth, scale, b_min, b_max, suffix,
                                     (int32_t)n_max, parent, token, nodes, branches, ws.ptr, ws.bytes, s);
-          }), "cure_repair_tree");
+          }, ws.enqueue), "cure_repair_tree");
     return out.take();
   });
 }

@@ -74,19 +74,21 @@ def test_logits_views_and_scalar_forms():
         pc.cure_margins(x.double())
 
 
-@pytest.mark.gpu
-def test_threads_on_streams_of_their_own():
-    """Calls of several threads, each on its own stream and with workspaces that grow between calls."""
+def _check_threads(stream):
+    """Calls of four threads, with workspaces that grow between calls, against calls made alone."""
     xs = [torch.randn(b, 16, 40000, device="cuda") for b in (1, 2, 4, 8)]
     want = [pc.cure_margins(x, 16, repair_budget=8, branch_depth=2) for x in xs]
     torch.cuda.synchronize()
     wrong = []
 
     def work():
-        with torch.cuda.stream(torch.cuda.Stream()):
-            for x, w in zip(xs, want):
-                got = pc.cure_margins(x, 16, repair_budget=8, branch_depth=2)
-                wrong.extend(k for k in w if not torch.equal(got[k], w[k]))
+        try:
+            with torch.cuda.stream(stream or torch.cuda.Stream()):
+                for x, w in list(zip(xs, want)) * 4:
+                    got = pc.cure_margins(x, 16, repair_budget=8, branch_depth=2)
+                    wrong.extend(k for k in w if not torch.equal(got[k], w[k]))
+        except Exception as e:
+            wrong.append(repr(e))
 
     threads = [threading.Thread(target=work) for _ in range(4)]
     for t in threads:
@@ -94,3 +96,13 @@ def test_threads_on_streams_of_their_own():
     for t in threads:
         t.join()
     assert not wrong
+
+
+@pytest.mark.gpu
+def test_threads_on_streams_of_their_own():
+    _check_threads(None)
+
+
+@pytest.mark.gpu
+def test_threads_on_one_stream():
+    _check_threads(torch.cuda.Stream())

@@ -1,7 +1,7 @@
-"""The Python binding's use of the interpreter lock, on the CPU.
+"""The Python binding's use of the interpreter lock and of its workspaces, on the CPU.
 
-A stub (binding_stub.cpp) stands in for the stream look-up, and fake tensors for the
-GPU's. Each check runs in a process of its own, since a fault here ends the process.
+A stub (binding_stub.cpp) stands in for the stream look-up and for the library's calls,
+and fake tensors for the GPU's. Each check runs in a process of its own, since a fault here ends the process.
 """
 
 import os
@@ -12,6 +12,8 @@ import textwrap
 import pytest
 import torch
 from torch.utils import cpp_extension
+
+from paper_2608_00531_amd import build as pbuild
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
@@ -29,7 +31,7 @@ import paper_2608_00531_amd as pc
 def stub(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("stub") / "stub.so")
     cmd = ["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, "-I", pbuild.INCLUDE]
     for path in cpp_extension.include_paths("cuda"):
         cmd += ["-isystem", path]
     res = subprocess.run(cmd + [os.path.join(HERE, "binding_stub.cpp"), "-o", out], capture_output=True, text=True)
@@ -71,3 +73,32 @@ def test_tensors_without_storage_raise(stub, name):
                 print("refused" if "data pointer" in str(e) else e)
         """, name)
     assert out == ["refused"]
+
+
+def test_calls_of_threads_on_one_stream_do_not_interleave(stub):
+    """A call's kernels hand data on through the stream's workspace, or through the library's scratch
+    array: no other call on it may enqueue between them."""
+    out = child(stub, """
+        import threading
+        errors = []
+        def work(k):
+            try:
+                with FakeTensorMode():
+                    f = lambda *s: torch.zeros(*s, device="cuda")
+                    i = lambda *s: torch.zeros(*s, dtype=torch.int32, device="cuda")
+                    x, n, t, off = f(2, 8, 40000), i(2), i(2, 8), torch.zeros(2, dtype=torch.int64, device="cuda")
+                    q, c = f(2, 8, 2, 64), f(3000, 2, 64)
+                    calls = [lambda: pc.cure_margins(x), lambda: pc.cure_margins_accept(x, t, t, n, n, 8),
+                             lambda: pc.cure_margins_noalloc(x),
+                             lambda: pc.cure_repair_tree(x, f(2, 8), t, n, t, 8, 2, 1.0),
+                             lambda: pc.cure_tree_attn(q, c, c, off, n, n, t, [1000, 1000], [8, 8], 1.0, kv_split=3)]
+                    for j in range(2 * len(calls)):
+                        calls[(j + (k % 2)) % len(calls)]()
+            except Exception as e:
+                errors.append(repr(e))
+        threads = [threading.Thread(target=work, args=(k,)) for k in range(6)]
+        for t in threads: t.start()
+        for t in threads: t.join()
+        print(stub.stub_calls(), stub.stub_overlaps(), *errors)
+        """)
+    assert out == ["60", "0"]
