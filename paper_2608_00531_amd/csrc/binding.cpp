@@ -93,31 +93,43 @@ at::Tensor empty(c10::IntArrayRef shape, at::ScalarType type, const at::Tensor& 
 }
 
 // Zero-filled device workspace, reused per (kind, device, stream) and grown when
-// a call needs more; lives as long as the process. The table is guarded by the
-// GIL. A call holds the tensor itself until its kernels are enqueued, in case
-// another thread on the same stream has it replaced by a larger one meanwhile,
-// and `enqueue` while it enqueues them: its kernels pass data through the
-// workspace, so another call's must not come between them on the stream.
+// a call needs more; lives as long as the process. A graph captured on the stream
+// holds its address, so a buffer that has become too small stays allocated, and
+// each one is twice the last or more: those kept take less than the one in use.
+// (Where twice the last does not fit on the GPU, what the call needs may.)
+// The table is guarded by the GIL. A call holds `enqueue` while it enqueues its
+// kernels: they pass data through the workspace, so another call's must not come
+// between them on the stream.
 struct Workspace {
   void* ptr;
   size_t bytes;
-  at::Tensor held;
   std::mutex* enqueue;
 };
 enum Kind { kMargins, kAttn, kRepair };
 Workspace workspace(Kind kind, const at::Tensor& like, void* stream, size_t bytes) {
-  if (bytes == 0) return {nullptr, 0, {}, nullptr};
+  if (bytes == 0) return {nullptr, 0, nullptr};
   struct Slot {
-    at::Tensor buffer;
+    std::vector<at::Tensor> buffers;   // the last one is in use
     std::mutex enqueue;
   };
   static auto* kept = new std::map<std::tuple<int, int, void*>, Slot>;
   Slot& slot = (*kept)[{(int)kind, (int)like.device().index(), stream}];
-  at::Tensor& ws = slot.buffer;
-  if (!ws.defined() || (size_t)ws.numel() < bytes)
-    ws = at::zeros({(int64_t)std::max<size_t>(bytes, 256)},
-                   at::TensorOptions().dtype(at::kByte).device(like.device()));
-  return {ws.data_ptr(), (size_t)ws.numel(), ws, &slot.enqueue};
+  const size_t had = slot.buffers.empty() ? 0 : (size_t)slot.buffers.back().numel();
+  if (had < bytes) {
+    const auto zeros = [&](size_t n) {
+      return at::zeros({(int64_t)n}, at::TensorOptions().dtype(at::kByte).device(like.device()));
+    };
+    at::Tensor grown;
+    try {
+      grown = zeros(std::max<size_t>({bytes, 2 * had, 256}));
+    } catch (const c10::OutOfMemoryError&) {
+      if (2 * had <= bytes) throw;
+      grown = zeros(bytes);
+    }
+    slot.buffers.push_back(std::move(grown));
+  }
+  const at::Tensor& ws = slot.buffers.back();
+  return {ws.data_ptr(), (size_t)ws.numel(), &slot.enqueue};
 }
 // The same for the scratch array inside the library that cure_margins_noalloc
 // calls share.

@@ -106,3 +106,27 @@ def test_threads_on_streams_of_their_own():
 @pytest.mark.gpu
 def test_threads_on_one_stream():
     _check_threads(torch.cuda.Stream())
+
+
+@pytest.mark.gpu
+def test_larger_calls_between_capture_and_replay():
+    """A graph keeps the workspace it was captured with: a larger call on its stream does not hand that
+    memory to other tensors."""
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    x, big = torch.randn(2, 16, 40000, device="cuda"), torch.randn(60, 16, 40000, device="cuda")
+    want = pc.cure_margins(x, 16, repair_budget=8, branch_depth=2)
+    with torch.cuda.stream(stream):
+        pc.cure_margins(x, 16, repair_budget=8, branch_depth=2)
+        stream.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            got = pc.cure_margins(x, 16, repair_budget=8, branch_depth=2)
+        pc.cure_margins(big, 16, repair_budget=8, branch_depth=2)
+        stream.synchronize()
+        others = [torch.full((n,), 77, dtype=torch.uint8, device="cuda") for n in [512, 4096, 32768, 1 << 18] * 40]
+        for _ in range(3):
+            for t in got.values():
+                t.zero_()
+            graph.replay()
+            stream.synchronize()
+            assert all(torch.equal(got[k], want[k]) for k in want)
+            assert all(bool((t == 77).all()) for t in others)

@@ -102,3 +102,28 @@ def test_calls_of_threads_on_one_stream_do_not_interleave(stub):
         print(stub.stub_calls(), stub.stub_overlaps(), *errors)
         """)
     assert out == ["60", "0"]
+
+
+def test_a_workspace_that_was_handed_out_stays_allocated(stub):
+    """A captured graph replays with the workspace's address, whatever larger calls come after it. The
+    buffers kept for that are bounded by the one in use."""
+    out = child(stub, """
+        from torch.multiprocessing.reductions import StorageWeakRef
+        from torch.utils._python_dispatch import TorchDispatchMode
+        seen = []                                    # the byte buffers that were allocated
+        class Watch(TorchDispatchMode):
+            def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+                t = func(*args, **(kwargs or {}))
+                if isinstance(t, torch.Tensor) and t.dtype == torch.uint8:
+                    ref = StorageWeakRef(t.untyped_storage())
+                    if not any(ref == r for r, _ in seen):
+                        seen.append((ref, t.numel()))
+                return t
+        with FakeTensorMode(), Watch():
+            for batch in (1, 2, 3, 40, 41, 90):
+                pc.cure_margins(torch.zeros(batch, 8, 40000, device="cuda"))
+            need = pc.lib().cure_margins_workspace_size(90, 8, 40000)
+        print(any(r.expired() for r, _ in seen), len(seen), seen[-1][1] >= need,
+              sum(n for _, n in seen[:-1]) <= seen[-1][1])
+        """)
+    assert out[0] == "False" and int(out[1]) >= 3 and out[2:] == ["True", "True"]
