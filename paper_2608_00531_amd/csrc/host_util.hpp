@@ -16,6 +16,14 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
+// Whether work enqueued on the stream is being recorded into a graph.
+inline bool is_capturing(hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();               // the launch that follows reports what is wrong, if anything
+  return false;
+}
+
 // Converts the result of a kernel launch into a status code.
 inline cure_status launch_status() {
   return hipGetLastError() == hipSuccess ? CURE_OK : CURE_ERR_HIP;

@@ -68,7 +68,7 @@ struct Args {
 struct CompactArgs : Args {
   int32_t row_blocks;
   uint32_t unit[kMaxUnits / 2];      // unit u in half u % 2 of word u / 2: sequence | split << 6
-  int32_t seq_splits[64];            // splits the host gave each sequence
+  int32_t seq_splits[64];            // splits each sequence may have
 };
 
 // Where a workgroup works: kv-head hk, row block rb and split s of sequence b,
@@ -1988,20 +1988,33 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
   // dispatcher spreads over the XCDs and starts together, read the heads of
   // the same token range, so concurrent reads cover whole cache rows.
   dim3 grid(hkv * p.row_blocks, p.max_splits, batch);
-  // A ragged batch of up to 64 sequences is launched compactly (locate()).
+  // A ragged batch of up to 64 sequences is launched compactly (locate()). A launch
+  // that is being captured may be replayed when other sequences are the long ones, so
+  // there every sequence may take max_splits, and the splits that the host's sizes
+  // leave empty are listed behind the others. Replays of 16 sequences captured at 1k -
+  // 4k tokens, 48 nodes, with these lengths, these permuted, random ones: 67, 76 and 83
+  // us; with the splits in use alone 64, 92 and 93, as a full grid 77, 75 and 83 (8 of
+  // 2k - 8k, 80 nodes: 84, 136, 121; 83, 187, 185; 114, 121, 124).
   bool compact = path != Path::kValu && !p.uniform_splits && batch <= 64 && p.max_splits < 1024;
   if (compact) {
+    const bool captured = is_capturing(st);
     int units = 0;
+    const auto list = [&](int b, int i) {
+      compact = compact && units < kMaxUnits;
+      if (compact) a.unit[units >> 1] |= (uint32_t)(b | i << 6) << (16 * (units & 1));
+      ++units;
+    };
+    int used[64];
     for (int b = 0; b < batch && compact; ++b) {
       const int N = std::min(host_n_nodes[b], n_max);
       const int64_t T = (int64_t)host_ctx_len[b] + N;
       // A sequence without nodes has one unit, which reports its status.
-      const int splits = N > 0 ? (int)((T + p.tps - 1) / p.tps) : 1;
-      compact = units + splits <= kMaxUnits;
-      for (int i = 0; i < splits && compact; ++i, ++units)
-        a.unit[units >> 1] |= (uint32_t)(b | i << 6) << (16 * (units & 1));
-      a.seq_splits[b] = splits;
+      used[b] = N > 0 ? (int)((T + p.tps - 1) / p.tps) : 1;
+      for (int i = 0; i < used[b] && compact; ++i) list(b, i);
+      a.seq_splits[b] = captured ? p.max_splits : used[b];
     }
+    for (int b = 0; b < batch && captured; ++b)
+      for (int i = used[b]; i < p.max_splits && compact; ++i) list(b, i);
     a.row_blocks = p.row_blocks;
     compact = compact && (int64_t)units * hkv * p.row_blocks <= INT32_MAX;
     if (compact) grid = dim3((unsigned)(units * hkv * p.row_blocks));

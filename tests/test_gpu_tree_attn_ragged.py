@@ -92,3 +92,28 @@ def test_merges_of_many_rows(d, hkv, group, kv_split, ragged):
     torch.cuda.synchronize()
     assert st.tolist() == [pc.CURE_OK] * batch
     check_attn(w, o, lse, *oracle_attn(w, sample=sample), sample=sample)
+
+
+@pytest.mark.parametrize("dtype,group,d", [("bf16", 4, 128), ("bf16", 12, 64), ("f32", 2, 128)])
+@pytest.mark.parametrize("host", ["swapped", "shorter"])
+def test_a_captured_launch_replays_with_other_lengths(dtype, group, d, host):
+    ctx, nodes = [1500, 300, 2600, 65], [16, 12, 16, 5]
+    w = general_tree_workload(26, 4, 2, group, d, nodes, ctx, "forest", dtype=dtype)
+    dev, ref = upload(w), oracle_attn(w)
+    hc, hn = (ctx[::-1], nodes[::-1]) if host == "swapped" else ([40, 0, 1900, 65], [1, 0, 16, 5])
+    call = lambda: pc.cure_tree_attn(dev["q"], dev["k"], dev["v"], dev["kv_off"], dev["ctx_len"], dev["n_nodes"],
+                                     dev["parent"], hc, hn, w.scale)
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        call()
+        stream.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            o, lse, st = call()
+        for _ in range(3):
+            call()
+            o.zero_(), lse.zero_()
+            graph.replay()
+            stream.synchronize()
+            assert st.tolist() == [pc.CURE_OK] * 4
+            check_attn(w, o, lse, *ref)

@@ -1,0 +1,76 @@
+"""Which kernels a tree-attention call launches, and with how many workgroups, on the CPU.
+
+A stub of the HIP runtime (launch_stub.cpp) records the launches of the built library in a
+process of its own; nothing runs on a GPU.
+"""
+
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_2608_00531_amd import build as pbuild
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+CHILD = """
+import ctypes as c, json, sys
+stub = c.CDLL(sys.argv[1], c.RTLD_GLOBAL)            # before the library's own HIP runtime
+stub.stub_launches.restype = c.c_char_p
+lib = c.CDLL(sys.argv[2])
+p, i, f, z = c.c_void_p, c.c_int32, c.c_float, c.c_size_t
+attn = lib.cure_tree_attn
+attn.argtypes = [p] * 5 + [i] * 6 + [f] + [p] * 4 + [i, p, p, i, c.c_uint32, p, p, z, p]
+def call(ctx, nodes, hq, hkv, d, dtype="bf16", kv_split=0, capturing=False):
+    array = lambda v: (i * len(v))(*v)
+    t, b = 4096, len(ctx)
+    stub.stub_reset(int(capturing))
+    code = 0 if dtype == "f32" else 1
+    status = attn(t, t, t, t, t, code, code, b, hq, hkv, d, 0.125, t, t, t, t, max(nodes), array(ctx),
+                  array(nodes), kv_split, 0, t, t, 1 << 60, None)
+    return status, [l.split() for l in stub.stub_launches().decode().splitlines()]
+print(json.dumps([call(**kw) for kw in json.loads(sys.argv[3])]))
+"""
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    stub = str(tmp_path_factory.mktemp("stub") / "launch_stub.so")
+    res = subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", os.path.join(HERE, "launch_stub.cpp"),
+                          "-o", stub], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+
+    def run(*calls):
+        """Per call: its kernels as (mangled name, grid, threads per workgroup)."""
+        res = subprocess.run([sys.executable, "-c", CHILD, stub, pbuild.LIB_PATH, json.dumps(calls)],
+                             capture_output=True, text=True, timeout=300)
+        assert res.returncode == 0, res.stdout + res.stderr
+        out = json.loads(res.stdout)
+        assert all(status == 0 for status, _ in out), out
+        return [[(l[0], tuple(map(int, l[1:4])), int(l[4])) for l in got] for _, got in out]
+    return run
+
+
+def is_compact(launch):
+    return "CompactArgs" in launch[0]
+
+
+# Eight sequences of 100 to 4000 tokens and 16 nodes, 8 kv-heads: forced splits of 512 tokens.
+RAGGED = dict(ctx=[4000, 100, 900, 1500, 2000, 300, 3000, 600], nodes=[16] * 8, hq=32, hkv=8, d=128, kv_split=8)
+SPLITS = [-(-(c + 16) // 512) for c in RAGGED["ctx"]]
+
+
+def test_a_captured_ragged_launch_has_room_for_other_lengths(launches):
+    """A launch that is replayed may meet a sequence that has grown since: each one has the launch's
+    largest split count at its disposal, where a call that runs once holds only the splits in use."""
+    eager, captured = launches(RAGGED, dict(RAGGED, capturing=True))
+    assert max(SPLITS) == 8 and sum(SPLITS) < 64
+    assert is_compact(eager[0]) and eager[0][1] == (sum(SPLITS) * 8, 1, 1)
+    assert is_compact(captured[0]) and captured[0][1] == (8 * 8 * 8, 1, 1)
+    # More than the table holds: the grid over sequences and splits.
+    many = dict(RAGGED, ctx=RAGGED["ctx"] * 3, nodes=[16] * 24, kv_split=32)
+    eager, captured = launches(many, dict(many, capturing=True))
+    assert is_compact(eager[0])
+    assert not is_compact(captured[0]) and captured[0][1] == (8, 32, 24)
