@@ -1660,7 +1660,7 @@ struct Plan {
   bool rows16;        // MFMA kernel with 16 query rows per wave
   bool rows64;        // head dim 64 beyond 128 rows: tree_attn_rg with two or three row groups
   bool rows48;        // MFMA kernel with three 16-row groups per wave (tree_attn_rg)
-  int nw;             // waves per workgroup (MFMA kernel)
+  int nw;             // waves per workgroup
   int rows_per_wg;
   int row_blocks;
   int tps;
@@ -2016,7 +2016,8 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
     for (int b = 0; b < batch && captured; ++b)
       for (int i = used[b]; i < p.max_splits && compact; ++i) list(b, i);
     a.row_blocks = p.row_blocks;
-    compact = compact && (int64_t)units * hkv * p.row_blocks <= INT32_MAX;
+    // The runtime takes fewer than 2^32 threads in a grid dimension.
+    compact = compact && (int64_t)units * hkv * p.row_blocks * 64 * p.nw < (int64_t(1) << 32);
     if (compact) grid = dim3((unsigned)(units * hkv * p.row_blocks));
   }
   const Args& full = a;

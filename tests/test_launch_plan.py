@@ -74,3 +74,15 @@ def test_a_captured_ragged_launch_has_room_for_other_lengths(launches):
     eager, captured = launches(many, dict(many, capturing=True))
     assert is_compact(eager[0])
     assert not is_compact(captured[0]) and captured[0][1] == (8, 32, 24)
+
+
+def test_grids_stay_below_the_runtimes_limit_of_threads(launches):
+    """The runtime takes fewer than 2^32 threads in each grid dimension. 443 splits on 32768 kv-heads are
+    14.5 million workgroups of 512 threads: a grid over sequences and splits."""
+    call = dict(ctx=[384] * 63 + [64], nodes=[16] * 64, hq=32768, hkv=32768, d=64, kv_split=7)
+    few = dict(call, hq=8192, hkv=8192)
+    for got in launches(call, dict(call, capturing=True), few):
+        assert all(n * threads < 2 ** 32 for _, grid, threads in got for n in grid)
+    wide, narrow = launches(call, few)
+    assert not is_compact(wide[0]) and wide[0][1] == (32768, 7, 64)
+    assert is_compact(narrow[0]) and narrow[0][1] == (443 * 8192, 1, 1)
