@@ -210,6 +210,10 @@ cure_status cure_margins_noalloc(const void* logits, int32_t dtype, int32_t batc
  * q, k, v 16 bytes and o 8 bytes (bf16 out) or 16 bytes (fp32 out).
  * fp32 inputs run on the fp32 matrix instructions when q, k, v and o have that
  * alignment, and on the vector-ALU kernel otherwise.
+ * The bf16 matrix-core kernels address a sequence's rows with 32-bit offsets:
+ * (ctx_len + n_nodes + 64) * hkv * d * 2 bytes must stay below 2^31. Calls whose
+ * host copies reach that take the vector-ALU kernel; where the device's sizes
+ * exceed the host's copies, they must not pass it.
  */
 size_t cure_tree_attn_workspace_size(int32_t batch, int32_t hq, int32_t hkv, int32_t d,
                                      int32_t n_max, const int32_t* host_ctx_len,

@@ -1243,11 +1243,13 @@ void tree_attn_f32(A a) {
   const int begin = s * a.tps;
   const int end = (s == S - 1) ? T : begin + a.tps;
 
-  // The tile DMA of the bf16 kernels: per lane and 1 KB block, the byte offset
-  // of its source chunk for tile start 0; rows past the sequence read as zeros.
+  // The tile DMA of the bf16 kernels, with the tile's own rows as the buffer
+  // resource, whose base moves on by a tile with each call: the device's lengths
+  // may exceed the host's copies, and fp32 rows soon pass what 32-bit offsets
+  // from the start of a sequence reach. Rows past the sequence read as zeros, and
+  // a tile at or past the split's end has none.
   const uint32_t tok_bytes = (uint32_t)(a.hkv * G::kRowBytes);
-  const uint32_t seq_bytes = (uint32_t)T * tok_bytes;
-  uint32_t src_off[G::kDmaPerWave];
+  uint32_t src_off[G::kDmaPerWave];                // per lane and 1 KB block
 #pragma unroll
   for (int j = 0; j < G::kDmaPerWave; ++j) {
     const int byte = (wave * G::kDmaPerWave + j) * 1024 + lane * 16;
@@ -1255,16 +1257,18 @@ void tree_attn_f32(A a) {
     const int pchunk = (byte % G::kRowBytes) >> 4;
     src_off[j] = (uint32_t)row * tok_bytes + (uint32_t)(hk * G::kRowBytes + ((pchunk ^ (row & 15)) << 4));
   }
-  const i32x4 rk4 = raw_rsrc(reinterpret_cast<const float*>(a.k) + off * a.hkv * D, seq_bytes);
-  const i32x4 rv4 = raw_rsrc(reinterpret_cast<const float*>(a.v) + off * a.hkv * D, seq_bytes);
+  const char* k_tile = reinterpret_cast<const char*>(a.k) + (off + begin) * (int64_t)tok_bytes;
+  const char* v_tile = reinterpret_cast<const char*>(a.v) + (off + begin) * (int64_t)tok_bytes;
   auto dma_tile = [&](int buf, int t0) {
-    const bool live = t0 < end;
+    const uint32_t bytes = t0 < end ? (uint32_t)min(T - t0, G::kTok) * tok_bytes : 0u;
+    const i32x4 rk4 = raw_rsrc(k_tile, bytes), rv4 = raw_rsrc(v_tile, bytes);
+    k_tile += (int64_t)G::kTok * tok_bytes;
+    v_tile += (int64_t)G::kTok * tok_bytes;
 #pragma unroll
     for (int j = 0; j < G::kDmaPerWave; ++j) {
-      const uint32_t voff = live ? src_off[j] + (uint32_t)t0 * tok_bytes : kOobOffset;
       const int blk = (wave * G::kDmaPerWave + j) * 1024;
-      dma16(lds_addr(&s_kv[buf][0][blk]), voff, rk4);
-      dma16(lds_addr(&s_kv[buf][1][blk]), voff, rv4);
+      dma16(lds_addr(&s_kv[buf][0][blk]), src_off[j], rk4);
+      dma16(lds_addr(&s_kv[buf][1][blk]), src_off[j], rv4);
     }
   };
   dma_tile(0, begin);
@@ -1855,20 +1859,20 @@ size_t plan_workspace(const Plan& p, int32_t batch, int32_t hq, int32_t d, int32
   return align_up(parts * d * sizeof(float), 256) + align_up(parts * sizeof(float), 256);
 }
 
-// The kernel family of a call, from its types, sizes and alignment. Every
-// matrix-core kernel addresses a sequence's K/V rows with 32-bit byte offsets.
-//  * bf16: takes the row maximum on raw scores, so scale > 0; operands that are
-//    not 16-byte aligned are refused later on.
+// The kernel family of a call, from its types, sizes and alignment.
+//  * bf16: addresses a sequence's K/V rows with 32-bit byte offsets and takes the
+//    row maximum on raw scores, so scale > 0; operands that are not 16-byte
+//    aligned are refused later on.
 //  * fp32: any finite scale; operands that are not 16-byte aligned (o: 8 bytes
 //    for a bf16 output) stay on the vector-ALU kernel, which takes them all.
 Path choose_path(int32_t dtype, int32_t out_dtype, int32_t d, int32_t hkv, float scale,
                  uint32_t flags, int64_t t_max, const void* q, const void* k, const void* v,
                  const void* o) {
-  const int64_t elem = dtype == CURE_BF16 ? 2 : 4;
-  if ((flags & CURE_ATTN_FORCE_VALU) || !std::isfinite(scale) ||
-      (t_max + kTile) * hkv * d * elem >= (int64_t(1) << 31))
-    return Path::kValu;
-  if (dtype == CURE_BF16) return scale > 0.f ? Path::kBf16 : Path::kValu;
+  if ((flags & CURE_ATTN_FORCE_VALU) || !std::isfinite(scale)) return Path::kValu;
+  if (dtype == CURE_BF16) {
+    const bool reach = (t_max + kTile) * hkv * d * 2 < (int64_t(1) << 31);
+    return scale > 0.f && reach ? Path::kBf16 : Path::kValu;
+  }
   const uintptr_t in = reinterpret_cast<uintptr_t>(q) | reinterpret_cast<uintptr_t>(k) |
                        reinterpret_cast<uintptr_t>(v);
   const uintptr_t out = reinterpret_cast<uintptr_t>(o) % (out_dtype == CURE_BF16 ? 8 : 16);

@@ -93,3 +93,27 @@ def test_malformed_tree_status():
     w.parent[1, 4] = 3
     ref_o, ref_l = oracle_attn(w)
     check_attn(w, o, lse, ref_o, ref_l, sample=[(b, n) for b in (0, 2) for n in range(int(w.n_nodes[b]))])
+
+
+@pytest.mark.parametrize("host", [300, 140000])
+def test_sequences_beyond_32_bit_offsets(host):
+    """A sequence whose K rows take more than 4 GiB, known to the host or not: sampled heads against
+    float64 sums (fp32 bars; 4.6 GB each of K and V)."""
+    say("f32 long", host)
+    ctx, n, h, d = 140000, 3, 64, 128
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    draw = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    q, k, v = draw(1, n, h, d), draw(ctx + n, h, d), draw(ctx + n, h, d)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    o, lse, st = pc.cure_tree_attn(q, k, v, torch.zeros(1, dtype=torch.int64, device="cuda"),
+                                   torch.tensor([ctx], **i32), torch.tensor([n], **i32),
+                                   torch.tensor([[-1, 0, 1]], **i32), [host], [n], 0.125)
+    torch.cuda.synchronize()
+    assert st.tolist() == [pc.CURE_OK]
+    hidden = torch.ones(n, n, dtype=torch.bool, device="cuda").triu(1)
+    for i in (0, 31, 63):
+        x = q[0, :, i].double() @ k[:, i].double().t().contiguous() * 0.125
+        x[:, ctx:].masked_fill_(hidden, -float("inf"))
+        want = torch.softmax(x, dim=1) @ v[:, i].double()
+        assert float((o[0, :, i].double() - want).abs().max()) <= 1e-5
+        assert float((lse[0, :, i].double() - torch.logsumexp(x, dim=1)).abs().max()) <= 1e-4
