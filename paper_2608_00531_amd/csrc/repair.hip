@@ -334,9 +334,9 @@ __global__ __launch_bounds__(kThreads) void topk_chunk(Args a) {
   }
 
   // Lower bound on the chunk's 8th-best value: per wave, the smallest maximum
-  // of eight disjoint 8-lane groups (a group without entries gives -inf, no
-  // bound); then the largest bound over the waves.
-  float g = fmaxf(fmaxf(fmaxf(vmax[0], vmax[1]), fmaxf(vmax[2], vmax[3])), fx);
+  // of eight disjoint 8-lane groups (a group without entries, or of NaNs alone,
+  // gives -inf, no bound); then the largest bound over the waves.
+  float g = fmaxf(fmaxf(fmaxf(vmax[0], vmax[1]), fmaxf(vmax[2], vmax[3])), fmaxf(fx, -INFINITY));
   g = fmaxf(g, partner<1>(g));
   g = fmaxf(g, partner<2>(g));
   g = fmaxf(g, partner<4>(g));
@@ -374,7 +374,7 @@ __global__ __launch_bounds__(kThreads) void topk_chunk(Args a) {
     }
   } else {
     uint32_t taken = 0;
-    bool x_taken = ex >= n;
+    bool x_taken = !(fx >= -INFINITY) | (ex >= n);       // a NaN never ranks, as in the vectors
     for (int r = 0; r < kTopK; ++r) {
       float bv = x_taken ? -INFINITY : fx;
       int bi = x_taken ? INT32_MAX : begin + ex;

@@ -70,3 +70,26 @@ def test_repair_trees_on_rows_that_start_anywhere(dtype, vocab):
         say("repair", dtype, vocab, "offset", off)
         run_case(blk, tau=1.5, budget=16, depth=2, scale=1.0, b_min=1, b_max=5,
                  logits_dev=shifted(blk.logits, dtype, off))
+
+
+@pytest.mark.parametrize("dtype,off", [("bf16", 1), ("bf16", 5), ("f32", 1), ("f32", 3)])
+def test_a_nan_beside_the_vectors_hides_no_other_entry(dtype, off):
+    """The ranking passes over a NaN: one among a row's first or last entries leaves the tree as if it
+    were -inf, also where many equal values send a wave the long way round."""
+    say("repair nan", dtype, off)
+    vocab, head = 8203, (8 if dtype == "bf16" else 4) - off
+    trees = []
+    for value in (np.nan, -np.inf):
+        x = np.full((1, 1, vocab), -4.0, np.float32)
+        x[0, 0, 600:1000] = 2.0
+        x[0, 0, head:head + 3] = [9.0, 8.0, 7.0]              # in the first lane's vector, like the NaN's lane
+        x[0, 0, [0, vocab - 1]] = value
+        t = torch.from_numpy(x).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+        buf = torch.zeros(vocab + 16, dtype=t.dtype, device="cuda")
+        row = buf[off:off + vocab].view(1, 1, vocab).copy_(t)
+        i32 = dict(dtype=torch.int32, device="cuda")
+        trees.append(pc.cure_repair_tree(row, torch.zeros(1, 1, device="cuda"), torch.zeros(1, 1, **i32),
+                                         torch.ones(1, **i32), torch.full((1, 1), 5000, **i32), 5, 1, 1.0,
+                                         b_min=5, b_max=5))
+    assert trees[0]["token"][0].tolist() == [5000, head, head + 1, head + 2, 600, 601]
+    assert all(torch.equal(trees[0][k], trees[1][k]) for k in trees[0])
