@@ -41,6 +41,7 @@ namespace {
 
 constexpr int kTile = 64;            // tokens per K/V tile
 constexpr int kMaxGridY = 65535;     // largest grid y (the split index)
+constexpr int kMaxBlocks = 65535;    // row blocks x kv-heads of a launch, at most
 constexpr int kMinTps = 256;         // tokens per split, at least
 constexpr int kMaxUnits = 512;       // entries of a compact launch's table
 constexpr int kAncWords = CURE_MAX_TREE_NODES / 64;
@@ -1814,10 +1815,11 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
       balance_rows(kRg64Rows4);
       tps = shortest_resident_split();
       const int64_t cost4 = cost(), tps4 = tps;
+      const bool room4 = (int64_t)p.row_blocks * hkv <= kMaxBlocks;
       balance_rows(256);
       slots = cus;
       tps = shortest_resident_split();
-      if (cost4 < cost()) {
+      if (cost4 < cost() && room4) {
         balance_rows(kRg64Rows4);
         tps = tps4;
       }
@@ -1948,7 +1950,7 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
   }
   const size_t need = plan_workspace(p, batch, hq, d, n_max);
   if (need > 0 && (!workspace || workspace_bytes < need)) return CURE_ERR_WORKSPACE;
-  if ((size_t)p.row_blocks * hkv > 65535 || batch > 65535) return CURE_ERR_UNSUPPORTED;
+  if ((int64_t)p.row_blocks * hkv > kMaxBlocks || batch > 65535) return CURE_ERR_UNSUPPORTED;
 
   CompactArgs a{};                      // its Args part serves full launches
   a.q = q;

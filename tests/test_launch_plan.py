@@ -86,3 +86,12 @@ def test_grids_stay_below_the_runtimes_limit_of_threads(launches):
     wide, narrow = launches(call, few)
     assert not is_compact(wide[0]) and wide[0][1] == (32768, 7, 64)
     assert is_compact(narrow[0]) and narrow[0][1] == (443 * 8192, 1, 1)
+
+
+def test_row_blocks_of_many_heads_stay_within_the_launch(launches):
+    """960 rows at head dim 64 fill the chip better in five blocks of 192 than in four of 240, but a launch
+    holds at most 65535 row blocks x kv-heads: 14000 kv-heads take four."""
+    call = dict(ctx=[100], nodes=[240], hq=56000, hkv=14000, d=64)
+    many, few = launches(call, dict(call, hq=5600, hkv=1400))
+    assert many[0][1:] == ((4 * 14000, 1, 1), 512)
+    assert few[0][1:] == ((5 * 1400, 1, 1), 256)
