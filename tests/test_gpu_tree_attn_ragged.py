@@ -50,11 +50,16 @@ def test_batches_around_the_list_of_sequences(batch, dtype):
     check(w, upload(w), oracle_attn(w))
 
 
-@pytest.mark.parametrize("kv_split", [100, 200])
-def test_more_splits_than_the_list_holds(kv_split):
-    # Sequences of 12800 and about 6400 tokens in 64- or 128-token splits: 350 and 700 splits.
-    w = general_tree_workload(23, 4, 1, 2, 64, [6, 6, 3, 6], [12790, 6400, 6390, 6300], "uniform")
-    check(w, upload(w), oracle_attn(w), kv_split=kv_split)
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("last,listed", [(61, 511), (62, 512), (63, 513)])
+def test_splits_around_the_list(last, listed, dtype):
+    """The list holds 512 splits: one less, as many and one more. Sequences that take 64-token splits,
+    the longest one 200 of them, with some tokens in each one's last."""
+    splits, nodes = [200, 150, 100, last], [6, 6, 3, 6]
+    ctx = [64 * s - 30 - n for s, n in zip(splits, nodes)]
+    assert sum(-(-(c + n) // 64) for c, n in zip(ctx, nodes)) == listed
+    w = general_tree_workload(23, 4, 1, 2, 64, nodes, ctx, "uniform", dtype=dtype)
+    check(w, upload(w), oracle_attn(w), kv_split=200)
 
 
 @pytest.mark.parametrize("dtype,group", [("bf16", 4), ("f32", 2)])

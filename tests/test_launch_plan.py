@@ -76,6 +76,17 @@ def test_a_captured_ragged_launch_has_room_for_other_lengths(launches):
     assert not is_compact(captured[0]) and captured[0][1] == (8, 32, 24)
 
 
+def test_the_list_holds_512_splits(launches):
+    """Sequences of 200, 150, 100 and 61 to 63 splits of 64 tokens: listed up to 512 in all, a grid over
+    sequences and splits beyond."""
+    call = lambda last: dict(ctx=[64 * s - 36 for s in (200, 150, 100, last)], nodes=[6] * 4, hq=2, hkv=1, d=64,
+                             kv_split=200)
+    below, at, above = [got[0] for got in launches(call(61), call(62), call(63))]
+    assert is_compact(below) and below[1] == (511, 1, 1)
+    assert is_compact(at) and at[1] == (512, 1, 1)
+    assert not is_compact(above) and above[1] == (1, 200, 4)
+
+
 def test_grids_stay_below_the_runtimes_limit_of_threads(launches):
     """The runtime takes fewer than 2^32 threads in each grid dimension. 443 splits on 32768 kv-heads are
     14.5 million workgroups of 512 threads: a grid over sequences and splits."""
