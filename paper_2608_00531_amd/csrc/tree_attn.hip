@@ -10,7 +10,7 @@
 // of every tree node, packed node-major. Only tiles that reach the tree rows
 // at the tail of the sequence apply the ancestor bitmask.
 //
-// Four kernels compute a split:
+// Five kernels compute a split:
 //  * tree_attn_m16: bf16, scale > 0, head dim 128 (any row count, in
 //    balanced row blocks of up to 256 rows) or 64 (up to 128 rows). Scores
 //    are formed transposed, S^T = K Q^T, and the output as O^T = V^T P^T with
@@ -18,7 +18,9 @@
 //    DMA; V is read back transposed by the LDS transpose-read instruction in
 //    exactly the token order the score MFMA leaves P in registers.
 //  * tree_attn_rg: the same with two or three 16-row groups per wave, for head dim
-//    128 with 257 - 384 rows and head dim 64 beyond 128 rows.
+//    128 with 257 - 384 rows and head dim 64 beyond 128 rows, in blocks of up to 192.
+//  * tree_attn_mfma: the same with 32x32x16 MFMAs and 32 rows per wave, for head dim 64
+//    beyond 192 rows, in blocks of up to 256.
 //  * tree_attn_f32: fp32 on the fp32 matrix instructions, the same scheme with
 //    the rows or the tokens of a block dealt over four waves.
 //  * tree_attn_valu: fp32 or bf16, any supported shape, scale and alignment;
@@ -40,8 +42,8 @@ namespace cure {
 namespace {
 
 constexpr int kTile = 64;            // tokens per K/V tile
+constexpr int kStages = 2;           // K/V tile buffers in tree_attn_mfma's LDS ring
 constexpr int kMaxGridY = 65535;     // largest grid y (the split index)
-constexpr int kMaxBlocks = 65535;    // row blocks x kv-heads of a launch, at most
 constexpr int kMinTps = 256;         // tokens per split, at least
 constexpr int kMaxUnits = 512;       // entries of a compact launch's table
 constexpr int kAncWords = CURE_MAX_TREE_NODES / 64;
@@ -363,6 +365,7 @@ __global__ __launch_bounds__(256) void tree_attn_valu(Args a) {
 // s_waitcnt + barrier before any LDS read of the tile it uses.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
@@ -455,6 +458,301 @@ struct TileGeo {
 // vmcnt[3:0] in bits 3:0, vmcnt[5:4] in bits 15:14, expcnt in 6:4).
 constexpr int waitcnt_vm(int vm) { return (vm & 15) | ((vm >> 4) << 14) | (7 << 4); }
 constexpr uint32_t kOobOffset = 0x80000000u;   // past any sequence's buffer resource
+
+// ---------------------------------------------------------------------------
+// MFMA split kernel with 32 query rows per wave (v_mfma_f32_32x32x16_bf16), for
+// head dim 64 in blocks of up to 256 rows.
+//
+// Each of the NW waves owns 32 query rows; lane = query row in S^T, whose tile is 2
+// token blocks x D/16 k-steps, and O^T takes D/32 column blocks x 4 k-steps. Bound by
+// LDS reads, MFMA and softmax issue, so by the waves there are to overlap them: in 119
+// VGPRs two workgroups, sixteen waves, share a CU, which two 16-row groups per wave
+// (tree_attn_rg) need too many registers for. With the same splits, 8 sequences of 8k
+// tokens and 256 rows take 59.6 us here, 70.0 in eight waves of two groups and 73.5 in
+// two blocks of four waves; 16 of 2k - 8k and 400 rows 143.9, and 157.7 in four-wave
+// blocks.
+template <int D, int NW, int NBUF, class A>
+__global__ __launch_bounds__(64 * NW, NBUF > 2 ? 1 : 2) void tree_attn_mfma(A a) {
+  using G = TileGeo<D>;
+  constexpr int kKSteps = D / 16;                  // MFMA k-steps for Q K^T
+  constexpr int kDBlk = D / 32;                    // 32-column blocks of O^T
+  constexpr int kDmaPerWave = G::kBlocks / NW;     // DMA blocks per wave per tensor
+  // Each loop iteration waits until its tile has landed while the NBUF - 2
+  // tiles issued after it may still be in flight (2 instructions per block).
+  constexpr int kVmWait = waitcnt_vm((NBUF - 2) * 2 * kDmaPerWave);
+  static_assert((NBUF - 2) * 2 * kDmaPerWave < 64, "vmcnt holds 6 bits");
+  static_assert(G::kBlocks % NW == 0, "tile must split evenly across waves");
+
+  __shared__ int s_parent[CURE_MAX_TREE_NODES];
+  __shared__ unsigned long long s_anc[CURE_MAX_TREE_NODES][kAncWords];
+  __shared__ int s_bad;
+  __shared__ __attribute__((aligned(1024))) unsigned char s_k[NBUF][G::kTileBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char s_v[NBUF][G::kTileBytes];
+
+  const Place at = locate(a);
+  const int b = at.b, hk = at.hk, rb = at.rb, s = at.s;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int half = lane >> 5, col = lane & 31;
+
+  // This lane's query row, and its query loads: they need only the launch
+  // shape (rows past the sequence's nodes still lie inside q and are zeroed
+  // below), so they go out together with the loads of the sequence's sizes,
+  // as does each thread's parent entry for the tree.
+  const int R = rb * a.rows_per_wg + wave * 32 + col;
+  const bool r_in = R < a.n_max * a.group;
+  bf16x8 qreg[kKSteps];
+  {
+    const int qn = r_in ? R / a.group : 0;
+    const int qh = hk * a.group + (r_in ? R % a.group : 0);
+    const uint16_t* qrow = reinterpret_cast<const uint16_t*>(a.q) +
+                           (((int64_t)b * a.n_max + qn) * a.hq + qh) * D;
+#pragma unroll
+    for (int kk = 0; kk < kKSteps; ++kk) {
+      Pack8 p;
+      p.u = r_in ? *reinterpret_cast<const uint4*>(qrow + kk * 16 + half * 8)
+                 : make_uint4(0, 0, 0, 0);
+      qreg[kk] = p.v;
+    }
+  }
+  const int my_parent = tid < a.n_max ? a.parent[(int64_t)b * a.n_max + tid] : -1;
+
+  // The sequence's sizes and cache offset are independent loads: one round
+  // trip. The empty asm keeps the compiler from sinking the offset's load
+  // below the early exits (a second round trip).
+  const int n_raw = a.n_nodes[b];
+  const int L = a.ctx_len[b];
+  const int64_t off = a.kv_off[b];
+  asm volatile("" : : "s"(n_raw), "s"(L), "s"(off));
+  const int N = min(n_raw, a.n_max);
+  const int T = L + N;
+  const int S = split_count(T, N, a.tps, at.max_splits);
+  const int rows = N * a.group;
+  if (S == 0) {                         // no nodes: nothing to compute; the empty tree is valid
+    report_tree(a, b, true, s == 0 && hk == 0 && rb == 0);
+    return;
+  }
+  if (s >= S || rb * a.rows_per_wg >= rows) return;
+
+  const int begin = s * a.tps;
+  const int end = (s == S - 1) ? T : begin + a.tps;
+
+  // Buffer resources over this sequence's K and V rows (all kv-heads).
+  const uint32_t seq_bytes = (uint32_t)T * (uint32_t)(a.hkv * G::kRowBytes);
+  // Per lane and DMA block: byte offset of the source chunk for tile start 0.
+  uint32_t src_off[kDmaPerWave];
+#pragma unroll
+  for (int j = 0; j < kDmaPerWave; ++j) {
+    const int byte = (wave * kDmaPerWave + j) * 1024 + lane * 16;   // destination in tile
+    const int row = byte / G::kRowBytes;
+    const int pchunk = (byte % G::kRowBytes) >> 4;
+    const int lchunk = pchunk ^ G::swz(row);
+    src_off[j] = (uint32_t)((row * a.hkv + hk) * G::kRowBytes + (lchunk << 4));
+  }
+  const uint32_t tok_bytes = (uint32_t)(a.hkv * G::kRowBytes);
+  // A tile at or past the split's end is still issued (at an out-of-range
+  // offset) so that every iteration has the same number of DMAs in flight.
+  const i32x4 rk4 = raw_rsrc(reinterpret_cast<const uint16_t*>(a.k) + off * a.hkv * D, seq_bytes);
+  const i32x4 rv4 = raw_rsrc(reinterpret_cast<const uint16_t*>(a.v) + off * a.hkv * D, seq_bytes);
+  auto dma_tile = [&](int buf, int t0) {
+    const bool live = t0 < end;
+#pragma unroll
+    for (int j = 0; j < kDmaPerWave; ++j) {
+      const uint32_t voff = live ? src_off[j] + (uint32_t)t0 * tok_bytes : kOobOffset;
+      const int blk = (wave * kDmaPerWave + j) * 1024;
+      dma16(lds_addr(&s_k[buf][blk]), voff, rk4);
+      dma16(lds_addr(&s_v[buf][blk]), voff, rv4);
+    }
+  };
+
+  // The first tiles' DMA goes out before anything else this workgroup loads.
+#pragma unroll
+  for (int i = 0; i < NBUF - 1; ++i) dma_tile(i, begin + i * kTile);
+
+  const bool row_ok = R < rows;
+  const int n = row_ok ? R / a.group : 0;
+  const int head = hk * a.group + (row_ok ? R % a.group : 0);
+  const bool wave_active = rb * a.rows_per_wg + wave * 32 < rows;
+
+  // LDS byte offsets used by this lane, independent of the tile.
+  // K rows blk*32 + col, logical chunk 2*kk + half.
+  int k_row_base[2], k_swz[2];
+#pragma unroll
+  for (int blk = 0; blk < 2; ++blk) {
+    const int row = blk * 32 + col;
+    k_row_base[blk] = row * G::kRowBytes;
+    k_swz[blk] = G::swz(row) ^ half;
+  }
+  // V transposed reads: lane j of each 16-lane group reads 8 bytes at row
+  // (4*half + j/4) of a 4-row group, columns 4*(j%4) of a 16-column block.
+  const int j16 = lane & 15, g16 = (lane >> 4) & 1;
+  const int v_row_lane = 4 * half + (j16 >> 2);          // + 16*ks + 8*r
+  const int v_chunk_lane = 2 * g16 + ((j16 & 3) >> 1);   // + 4*i
+  const int v_byte_lane = (j16 & 1) * 8;
+
+  // Only a split that reaches the tree's own rows needs the ancestor masks
+  // (built while the first tile and the queries are in flight). The last
+  // split always does, and it reports the tree's status. With a malformed
+  // tree the other splits still run; the sequence's output is unspecified.
+  if (end > L) {
+    const bool ok = build_tree_loaded(N, my_parent, s_parent, s_anc, &s_bad);
+    report_tree(a, b, ok, s == S - 1 && hk == 0 && rb == 0);
+    if (!ok) {
+      __builtin_amdgcn_s_waitcnt(0);      // no DMA may land after the workgroup ends
+      return;
+    }
+  }
+
+  f32x16 oacc[kDBlk];
+#pragma unroll
+  for (int i = 0; i < kDBlk; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[i][r] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+  const float c = a.scale_log2;
+  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+
+  // Queries and the first tiles have landed. (This also tells the compiler
+  // that no load it issued is pending, so it adds no waits inside the loop.)
+  __builtin_amdgcn_s_waitcnt(0);
+  if (!row_ok) {
+#pragma unroll
+    for (int kk = 0; kk < kKSteps; ++kk) qreg[kk] = bf16x8{};
+  }
+  for (int t0 = begin, buf = 0; t0 < end; t0 += kTile, buf = buf + 1 == NBUF ? 0 : buf + 1) {
+    __builtin_amdgcn_s_waitcnt(kVmWait);  // this wave's DMA into `buf` has landed
+    __syncthreads();                      // everyone's has; the previous buffer is free
+    dma_tile(buf == 0 ? NBUF - 1 : buf - 1, t0 + (NBUF - 1) * kTile);
+    if (!wave_active) continue;
+    const unsigned char* kt = s_k[buf];
+    const unsigned char* vt = s_v[buf];
+
+    // S^T (tokens x query rows), raw dot products; two independent chains.
+    f32x16 sacc[2];
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sacc[blk][r] = 0.f;
+    // K operands are read one k-step ahead of the MFMAs that consume them.
+    Pack8 ka[2][2];
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk)
+      ka[0][blk].u = *reinterpret_cast<const uint4*>(kt + k_row_base[blk] + (k_swz[blk] << 4));
+#pragma unroll
+    for (int kk = 0; kk < kKSteps; ++kk) {
+      if (kk + 1 < kKSteps) {
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk)
+          ka[(kk + 1) & 1][blk].u = *reinterpret_cast<const uint4*>(
+              kt + k_row_base[blk] + (((2 * (kk + 1)) ^ k_swz[blk]) << 4));
+      }
+#pragma unroll
+      for (int blk = 0; blk < 2; ++blk)
+        sacc[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk & 1][blk].v, qreg[kk], sacc[blk], 0, 0, 0);
+    }
+    // Mask the tail, then the tile's row maximum (raw units; the scale is > 0).
+    if (t0 + kTile > L) {
+#pragma unroll
+      for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          sacc[blk][r] += mask_bias(t0 + blk * 32 + 8 * (r >> 2) + 4 * half + (r & 3), L, end, n, s_anc);
+    }
+    // Row maximum: one three-input max per two scores, in two chains.
+    float mb[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) mb[blk] = max3_raw(mb[blk], sacc[blk][r], sacc[blk][r + 1]);
+    const float m_tile = max_halves(max3_raw(mb[0], mb[1], mb[1])) * c;
+    // Lazy rescale: move the reference only when the maximum rises by > 2^8.
+    const bool grow = m_tile > m_run + kRescaleLog2;
+    if (__builtin_expect(__ballot(grow) != 0, 0)) {
+      if (grow) {
+        const float alpha = fast_exp2(m_run - m_tile);
+        l_run *= alpha;
+#pragma unroll
+        for (int i = 0; i < kDBlk; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) oacc[i][r] *= alpha;
+        m_run = m_tile;
+      }
+    }
+    const float nm = m_run == -INFINITY ? 0.f : -m_run;
+    bf16x8 pb[4];
+    float l0 = 0.f, l1 = 0.f;
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        bf16x8 v8;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v8[e] = (__bf16)fast_exp2(fmaf(sacc[blk][8 * j + e], c, nm));
+        pb[blk * 2 + j] = v8;
+        // Row sums of the probabilities as rounded for the MFMA (bf16 pairs).
+#pragma unroll
+        for (int e = 0; e < 8; e += 4) {
+          l0 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{v8[e], v8[e + 1]}, ones, l0, false);
+          l1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{v8[e + 2], v8[e + 3]}, ones, l1, false);
+        }
+      }
+    l_run += l0 + l1;
+
+    // O^T += V^T P^T; the D/32 column blocks are independent chains.
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+      for (int i = 0; i < kDBlk; ++i) {
+        Pack8 va;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+          const int row = 16 * ks + 8 * r + v_row_lane;
+          const int byte = G::offset(row, 4 * i + v_chunk_lane) + v_byte_lane;
+          va.h[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(vt + byte));
+        }
+        oacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va.v, pb[ks], oacc[i], 0, 0, 0);
+      }
+    }
+  }
+
+  __builtin_amdgcn_s_waitcnt(0);          // the ring's trailing DMAs land before exit
+  if (!row_ok) return;
+  const float l_tot = sum_halves(l_run);
+  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  const float lse_nat = l_tot > 0.f ? (m_run + log2f(l_tot)) * kLn2 : -INFINITY;
+  if (S == 1) {
+    const int64_t obase = (((int64_t)b * a.n_max + n) * a.hq + head) * D;
+#pragma unroll
+    for (int i = 0; i < kDBlk; ++i)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const int d0 = i * 32 + 8 * g4 + 4 * half;
+        const float x0 = oacc[i][4 * g4] * inv, x1 = oacc[i][4 * g4 + 1] * inv;
+        const float x2 = oacc[i][4 * g4 + 2] * inv, x3 = oacc[i][4 * g4 + 3] * inv;
+        if (a.out_bf16) {
+          uint2 pk;
+          pk.x = pack_bf16x2(x0, x1);
+          pk.y = pack_bf16x2(x2, x3);
+          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.o) + obase + d0) = pk;
+        } else {
+          *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.o) + obase + d0) =
+              make_float4(x0, x1, x2, x3);
+        }
+      }
+    if (half == 0 && a.lse) a.lse[((int64_t)b * a.n_max + n) * a.hq + head] = lse_nat;
+  } else {
+    const int64_t pi = part_index(a, b, head, n, s);
+#pragma unroll
+    for (int i = 0; i < kDBlk; ++i)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const int d0 = i * 32 + 8 * g4 + 4 * half;
+        *reinterpret_cast<float4*>(a.part_o + pi * D + d0) =
+            make_float4(oacc[i][4 * g4] * inv, oacc[i][4 * g4 + 1] * inv,
+                        oacc[i][4 * g4 + 2] * inv, oacc[i][4 * g4 + 3] * inv);
+      }
+    if (half == 0) a.part_lse[pi] = lse_nat;
+  }
+}
 
 // ---------------------------------------------------------------------------
 // MFMA split kernel with 16 query rows per wave (v_mfma_f32_16x16x32_bf16).
@@ -1663,7 +1961,8 @@ enum class Path { kValu, kF32, kBf16 };   // kernel family: vector ALU, fp32 or 
 struct Plan {
   Path path;
   bool rows16;        // MFMA kernel with 16 query rows per wave
-  bool rows64;        // head dim 64 beyond 128 rows: tree_attn_rg with two or three row groups
+  bool rows64;        // head dim 64 beyond 128 rows: tree_attn_rg with two or three row groups,
+  bool rows32;        // or the MFMA kernel with 32 query rows per wave
   bool rows48;        // MFMA kernel with three 16-row groups per wave (tree_attn_rg)
   int nw;             // waves per workgroup
   int rows_per_wg;
@@ -1678,7 +1977,7 @@ struct Plan {
 // tile; planned for 257 - 384 rows.
 constexpr int kRg3Waves = 8;
 constexpr int kRg3Rows = kRg3Waves * 48;
-// Head dim 64 beyond 128 rows: the most rows of a four-wave workgroup.
+// Head dim 64 beyond 128 rows: the most rows of a workgroup of tree_attn_rg.
 constexpr int kRg64Rows4 = 4 * 48;
 
 Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
@@ -1696,7 +1995,7 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
   // blocks of the 16-row kernel, 352 rows 139 against 151; at 224 and 256
   // rows the 16-row kernel's single block is ahead (103 vs 106, 109 vs 113).
   // Head dim 64: the 16-row kernel up to 128 rows, else two or three row groups
-  // per wave.
+  // per wave or 32 rows per wave.
   p.rows48 = mfma && d == 128 && rows > 256 && rows <= kRg3Rows;
   p.rows64 = mfma && d == 64 && rows > 128;
   p.rows16 = mfma && !p.rows48 && !p.rows64;
@@ -1795,35 +2094,6 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
     tps = make_plan(batch, hq, hkv, d, n_max, host_ctx_len, host_n_nodes, 0, Path::kBf16).tps;
   } else {
     tps = shortest_resident_split();
-    // Head dim 64 beyond 128 rows: tree_attn_rg with four waves of three row
-    // groups, two workgroups per CU, or with eight waves of two, one per CU. Rows
-    // that balance to blocks of at most 192 keep the split length for two per CU
-    // either way, and eight waves take them when one per CU holds the launch:
-    // with equal splits they start faster (4 sequences of 0.5k - 2k tokens, 192
-    // rows: 17.6 us a call against 19.2), and two four-wave workgroups fill a CU
-    // better (16 of 8k: 79.3 against 84.5). Other rows are cut into blocks of at
-    // most 256 for eight waves or of at most 192 for four, whichever gives the
-    // busiest SIMD fewer row groups x tiles: 16 sequences of 8k tokens, 512 rows
-    // 97 us in two blocks of 256 and 121 in three of 176 (half of the second
-    // round of CUs idle), 640 rows 158 in three of 224 and 126 in four of 160; 8
-    // of 8k, 256 rows 37 and 42.
-    if (p.rows64 && p.rows_per_wg > kRg64Rows4) {
-      const auto cost = [&]() {
-        const int64_t wgs = workgroups(tps), per_cu = std::min((wgs + cus - 1) / cus, slots / cus);
-        return (wgs + slots - 1) / slots * (tps / kTile) * per_cu * ((p.rows_per_wg / 16 + 3) / 4);
-      };
-      balance_rows(kRg64Rows4);
-      tps = shortest_resident_split();
-      const int64_t cost4 = cost(), tps4 = tps;
-      const bool room4 = (int64_t)p.row_blocks * hkv <= kMaxBlocks;
-      balance_rows(256);
-      slots = cus;
-      tps = shortest_resident_split();
-      if (cost4 < cost() && room4) {
-        balance_rows(kRg64Rows4);
-        tps = tps4;
-      }
-    }
     // A small launch (even the shortest splits leave most CUs idle, as for one
     // sequence) cuts the 16-row kernel's rows into more blocks, of at least 32
     // rows: the blocks of one kv-head and split are hkv workgroup ids apart,
@@ -1840,7 +2110,29 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
       }
     }
   }
-  if (p.rows64) p.nw = p.rows_per_wg > kRg64Rows4 || workgroups(tps) <= cus ? 8 : 4;
+  // Head dim 64 beyond 128 rows. Blocks of at most 192 rows: tree_attn_rg with eight
+  // waves of two row groups when one workgroup per CU holds the launch, and with four
+  // waves of three, two workgroups per CU, otherwise: with equal splits eight waves
+  // start faster (4 sequences of 0.5k - 2k tokens, 192 rows: 17.6 us a call against
+  // 19.2), and two four-wave workgroups fill a CU better (16 of 8k: 79.3 against 84.5).
+  // Rows that balance to larger blocks are cut that small when the launch stays within
+  // one workgroup per CU (one sequence of 2k, 256 rows: 16.6 against 18.4), and are left
+  // to tree_attn_mfma otherwise. Neither changes the splits: longer ones, for one
+  // workgroup per CU, were 0 - 25 % faster on short contexts, but the error against 64
+  // bits grew by up to 2.9 %: a row's probabilities are rounded to bf16 against the
+  // maximum over its split's first tile, and the largest one is exact when it is that
+  // maximum, which is rarer the longer a split is.
+  if (p.rows64 && p.rows_per_wg > kRg64Rows4) {
+    balance_rows(kRg64Rows4);
+    if (workgroups(tps) > cus) {
+      p.rows64 = false;
+      p.rows32 = true;
+      p.rows_per_wg = 256;
+      p.row_blocks = (rows + 255) / 256;
+      p.nw = 8;
+    }
+  }
+  if (p.rows64) p.nw = workgroups(tps) > cus ? 4 : 8;
   // Splits index the grid's y dimension (at most kMaxGridY).
   tps = std::max<int64_t>(tps, round_tile((t_max + kMaxGridY - 1) / kMaxGridY));
   p.tps = (int)std::min<int64_t>(tps, INT32_MAX / 2);
@@ -1950,7 +2242,7 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
   }
   const size_t need = plan_workspace(p, batch, hq, d, n_max);
   if (need > 0 && (!workspace || workspace_bytes < need)) return CURE_ERR_WORKSPACE;
-  if ((int64_t)p.row_blocks * hkv > kMaxBlocks || batch > 65535) return CURE_ERR_UNSUPPORTED;
+  if ((size_t)p.row_blocks * hkv > 65535 || batch > 65535) return CURE_ERR_UNSUPPORTED;
 
   CompactArgs a{};                      // its Args part serves full launches
   a.q = q;
@@ -2038,6 +2330,8 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
     if (d == 128 && p.nw == 8) CURE_ATTN(512, tree_attn_m16, 128, 8);
     else if (d == 128) CURE_ATTN(1024, tree_attn_m16, 128, 16);
     else CURE_ATTN(512, tree_attn_m16, 64, 8);
+  } else if (p.rows32) {
+    CURE_ATTN(512, tree_attn_mfma, 64, 8, kStages);
   } else if (p.rows64) {
     if (p.nw == 4) CURE_ATTN(256, tree_attn_rg, 64, 4, 3, 2, 4, 1, 2);
     else CURE_ATTN(512, tree_attn_rg, 64, 8, 2, 2, 8, 1, 3);

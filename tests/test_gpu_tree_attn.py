@@ -218,9 +218,9 @@ def test_row_blocking_and_wide_trees(hq, hkv, d, n_ufp, depth):
     # (32,8,128,16,4): 80 x 4 = 320 -> one block of the 48-row-per-wave kernel;
     # (8,8,128,16,15): 256 nodes (the maximum), G1 -> 16-row kernel, 16 waves;
     # (4,1,128,8,4): 48 x 4 = 192 -> 16-row kernel, 12 of 16 waves;
-    # (4,1,64,8,4): 192 rows at head dim 64 -> 32-row kernel;
+    # (4,1,64,8,4): 192 rows at head dim 64 -> two row groups per wave;
     # (32,8,128,2,4): 24 x 4 = 96 -> 16-row kernel, 6 of 8 waves;
-    # (64,8,128,8,4): 48 x 8 = 384 -> two 192-row blocks;
+    # (64,8,128,8,4): 48 x 8 = 384 -> one block of the 48-row-per-wave kernel;
     # (32,4,128,15,5): 91 x 8 = 728 -> three 256-row blocks, the last with 216
     #   rows (its 14th wave half full); hkv 4, so the blocks sit on different XCDs;
     # (32,8,64,4,4): 32 x 4 = 128 rows at head dim 64 -> 16-row kernel.

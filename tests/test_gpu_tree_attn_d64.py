@@ -1,8 +1,9 @@
 """GPU parity of the bf16 attention kernels for head dim 64 beyond 128 rows per kv-head.
 
-Blocks of up to 256 rows on eight waves of two 16-row groups, or of up to 192 rows
-on four waves of three: row counts around the groups and blocks of both, sequences
-with fewer nodes than the launch, against the float64 oracle on sampled nodes.
+Blocks of up to 192 rows on eight waves of two 16-row groups or on four of three, and
+blocks of up to 256 rows on eight waves of 32 rows: row counts around the groups and
+blocks of all, sequences with fewer nodes than the launch, against the float64 oracle
+on sampled nodes.
 """
 
 import math
@@ -18,10 +19,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("hkv,group,nodes,ctx", [
-    # up to 256 workgroups: eight waves, one block of 129 - 256 rows, then two and more
+    # up to 256 workgroups: eight waves of row groups, blocks of up to 192 rows
     (2, 1, [129, 144], [300, 64]), (1, 8, [17, 18], [700, 90]), (2, 4, [64, 33], [129, 1000]),
     (1, 4, [65, 20], [500, 500]), (1, 8, [100, 256], [10, 70]),
-    # more workgroups: four waves; 240 rows and 2048 are left to either
+    # more workgroups: four waves, and eight of 32 rows (200, 240, 256 and 2048 rows)
     (8, 4, [33, 48], [13000, 12800]), (8, 4, [48, 48], [25700, 0]), (4, 8, [25, 40], [14000, 13000]),
     (2, 8, [256, 199], [13000, 500]), (8, 4, [60, 49], [26000, 100])])
 @pytest.mark.parametrize("kv_split", [0, 3])
@@ -35,8 +36,8 @@ def test_row_groups_and_blocks(hkv, group, nodes, ctx, kv_split):
     check_attn(w, o, lse, *oracle_attn(w, sample=sample), sample=sample)
 
 
-@pytest.mark.parametrize("batch", [2, 40])             # 16 workgroups of eight waves, 320 of four
-@pytest.mark.parametrize("nodes", [33, 48])
+@pytest.mark.parametrize("batch", [2, 40])             # up to 32 workgroups, and 320 or more
+@pytest.mark.parametrize("nodes", [33, 48, 64])        # one block of 132, 192 and 256 rows (or two of 128)
 def test_probabilities_are_rounded_against_the_first_64_tokens(batch, nodes):
     """The output in fp32 against float64 sums of probabilities that are rounded to bf16 relative to
     each row's maximum over the split's first 64 tokens. A kernel's fp32 scores (relative error about

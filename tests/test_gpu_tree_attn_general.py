@@ -5,11 +5,10 @@ topologically ordered parent array: nested branches, wide sibling fans and
 several nodes attached straight after the context (parent -1). The interface
 takes any such array of up to 256 nodes. These cases draw random parent arrays
 of four shapes and run them through every attention kernel: the 16-row MFMA
-kernel (head dim 128 up to 256 rows and, in row blocks, beyond 336; head dim 64
-up to 128 rows), the kernel with three 16-row groups per wave (head dim 128,
-257 - 336 rows), the 32-row MFMA kernel (head dim 64 beyond 128 rows) and the
-vector-ALU kernel (bf16 forced, and fp32), against the float64 oracle element
-by element.
+kernel (head dim 128 up to 256 rows and, in row blocks, beyond 384; head dim 64
+up to 128 rows), the kernel with two or three 16-row groups per wave (head dim
+128 with 257 - 384 rows, head dim 64 beyond 128), the fp32 matrix-core kernel and
+the vector-ALU kernel (forced), against the float64 oracle element by element.
 """
 
 import numpy as np
@@ -80,12 +79,12 @@ STYLES = ("uniform", "nested", "fans", "forest")
 CASES = [
     (2, 1, 128, [256, 201], [700, 0]),       # 256 rows: 16-row kernel, 16 waves
     (1, 4, 128, [256, 130], [333, 1500]),    # 1024 rows: four 256-row blocks
-    (1, 8, 64, [256, 97], [64, 900]),        # 2048 rows at d 64: 32-row kernel, 8 blocks
-    (2, 4, 64, [100, 100], [1, 1200]),       # 400 rows at d 64: 32-row kernel
+    (1, 8, 64, [256, 97], [64, 900]),        # 2048 rows at d 64: row groups, 8 blocks
+    (2, 4, 64, [100, 100], [1, 1200]),       # 400 rows at d 64: row groups
     (8, 4, 128, [24, 9], [2048, 65]),        # 96 rows, GQA 4 (the Llama shape)
     (8, 4, 128, [48, 48], [1000, 2500]),     # 192 rows
     (8, 4, 128, [80, 61], [1300, 127]),      # 320 rows: 48-row waves
-    (2, 4, 128, [84, 70], [500, 3000]),      # 336 rows: the 48-row block's capacity
+    (2, 4, 128, [84, 70], [500, 3000]),      # 336 rows: 48-row waves
     (4, 8, 128, [32, 17], [900, 4000]),      # 256 rows at GQA 8
     (2, 1, 64, [200, 3], [500, 63]),         # 200 rows at d 64 and GQA 1
     (1, 8, 64, [16, 12], [128, 129]),        # 128 rows at d 64: 16-row kernel

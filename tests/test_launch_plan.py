@@ -87,6 +87,17 @@ def test_the_list_holds_512_splits(launches):
     assert not is_compact(above) and above[1] == (1, 200, 4)
 
 
+def test_the_list_holds_512_splits(launches):
+    """Sequences of 200, 150, 100 and 61 to 63 splits of 64 tokens: listed up to 512 in all, a grid over
+    sequences and splits beyond."""
+    call = lambda last: dict(ctx=[64 * s - 36 for s in (200, 150, 100, last)], nodes=[6] * 4, hq=2, hkv=1, d=64,
+                             kv_split=200)
+    below, at, above = [got[0] for got in launches(call(61), call(62), call(63))]
+    assert is_compact(below) and below[1] == (511, 1, 1)
+    assert is_compact(at) and at[1] == (512, 1, 1)
+    assert not is_compact(above) and above[1] == (1, 200, 4)
+
+
 def test_grids_stay_below_the_runtimes_limit_of_threads(launches):
     """The runtime takes fewer than 2^32 threads in each grid dimension. 443 splits on 32768 kv-heads are
     14.5 million workgroups of 512 threads: a grid over sequences and splits."""
@@ -100,9 +111,24 @@ def test_grids_stay_below_the_runtimes_limit_of_threads(launches):
 
 
 def test_row_blocks_of_many_heads_stay_within_the_launch(launches):
-    """960 rows at head dim 64 fill the chip better in five blocks of 192 than in four of 240, but a launch
-    holds at most 65535 row blocks x kv-heads: 14000 kv-heads take four."""
-    call = dict(ctx=[100], nodes=[240], hq=56000, hkv=14000, d=64)
-    many, few = launches(call, dict(call, hq=5600, hkv=1400))
-    assert many[0][1:] == ((4 * 14000, 1, 1), 512)
-    assert few[0][1:] == ((5 * 1400, 1, 1), 256)
+    """A launch holds at most 65535 row blocks x kv-heads: 960 rows of 14000 kv-heads fit it in four blocks of
+    256, not in five of 192."""
+    got, = launches(dict(ctx=[100], nodes=[240], hq=56000, hkv=14000, d=64))
+    assert got[0][1:] == ((4 * 14000, 1, 1), 512)
+
+
+def test_wide_trees_at_head_dim_64_keep_the_splits_of_two_workgroups_per_cu(launches):
+    """The split length decides which maximum a row's probabilities are rounded against. Whatever the kernel,
+    it is the shortest, in 64-token tiles, whose blocks of 256 rows stay within two a CU."""
+    call = lambda batch, tokens, nodes, hkv=8: dict(ctx=[tokens - nodes] * batch, nodes=[nodes] * batch,
+                                                    hq=4 * hkv, hkv=hkv, d=64)
+    shapes = [(8, 8192, 64, 8), (8, 8192, 50, 8), (4, 8192, 100, 8), (1, 2048, 64, 8), (1, 2048, 100, 8),
+              (16, 1024, 64, 4), (8, 4096, 48, 8), (2, 1024, 80, 8)]
+    for (batch, tokens, nodes, hkv), got in zip(shapes, launches(*[call(*s) for s in shapes])):
+        blocks = batch * hkv * -(-4 * nodes // 256)
+        tiles = next(t for t in range(4, tokens // 64 + 1) if blocks * -(-tokens // (64 * t)) <= 512)
+        (name, grid, threads), splits = got[0], -(-tokens // (64 * tiles))
+        assert grid[1:] == (splits, batch), (batch, tokens, nodes)
+        wide = -(-4 * nodes // -(-4 * nodes // 256)) > 192         # blocks of more than 192 rows, balanced
+        small = batch * splits * hkv * -(-4 * nodes // 192) <= 256
+        assert ("tree_attn_mfma" in name) == (wide and not small), (name, batch, tokens, nodes)
