@@ -1970,6 +1970,7 @@ struct Plan {
   int tps;
   int max_splits;
   bool uniform_splits;  // every sequence with nodes has max_splits splits (host sizes)
+  int wgs_per_cu;       // workgroups of the kernel that a CU holds at once, by LDS and registers
 };
 
 // The three-row-group kernel as instantiated: 8 waves of up to 48 query rows
@@ -2133,6 +2134,8 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
     }
   }
   if (p.rows64) p.nw = workgroups(tps) > cus ? 4 : 8;
+  if (p.rows16 || p.rows64) p.wgs_per_cu = p.nw == (p.rows64 ? 4 : 8) ? 2 : 1;
+  else p.wgs_per_cu = p.rows48 || (path == Path::kF32 && wgs_per_cu == 1) ? 1 : 2;
   // Splits index the grid's y dimension (at most kMaxGridY).
   tps = std::max<int64_t>(tps, round_tile((t_max + kMaxGridY - 1) / kMaxGridY));
   p.tps = (int)std::min<int64_t>(tps, INT32_MAX / 2);
@@ -2286,37 +2289,56 @@ extern "C" cure_status cure_tree_attn(const void* q, const void* k, const void* 
   // dispatcher spreads over the XCDs and starts together, read the heads of
   // the same token range, so concurrent reads cover whole cache rows.
   dim3 grid(hkv * p.row_blocks, p.max_splits, batch);
-  // A ragged batch of up to 64 sequences is launched compactly (locate()). A launch
-  // that is being captured may be replayed when other sequences are the long ones, so
-  // there every sequence may take max_splits, and the splits that the host's sizes
+  // A ragged batch of up to 64 sequences may be launched compactly (locate()), where
+  // workgroups without work would delay others or put two on one CU beside an idle one.
+  // They do neither when the CUs hold the full grid one each, nor when they hold it all at
+  // once and have to take two each anyway, and two small ones on a CU (few rows, shortest
+  // splits) cost little; the compact form's look-ups then cost 0.3 - 0.7 us, and with two
+  // each it starts less evenly. Full and compact, us a call: 2 sequences of 2k - 3k tokens,
+  // 6 nodes, head dim 64, 9.0 and 9.4; 4 of 0.9k - 1.8k, 100 nodes, 29.3 and 32.3; 8 of
+  // 0.4k - 2.8k, 16 nodes, 32 rows a block, 11.7 and 12.4; but 3 of 1k - 2.6k, 32 nodes,
+  // head dim 128, 21.3 and 19.4, 5 of 1k - 6.9k, 6 nodes, 16 heads in long splits, 39.8 and
+  // 34.3, and fp32, 8 of 0.4k - 2.8k, 16 nodes, 32.0 and 23.5.
+  // A launch that is being captured may be replayed when other sequences are the long
+  // ones, so there every sequence may take max_splits, and the splits that the host's sizes
   // leave empty are listed behind the others. Replays of 16 sequences captured at 1k -
   // 4k tokens, 48 nodes, with these lengths, these permuted, random ones: 67, 76 and 83
   // us; with the splits in use alone 64, 92 and 93, as a full grid 77, 75 and 83 (8 of
   // 2k - 8k, 80 nodes: 84, 136, 121; 83, 187, 185; 114, 121, 124).
-  bool compact = path != Path::kValu && !p.uniform_splits && batch <= 64 && p.max_splits < 1024;
+  bool compact = path != Path::kValu && !p.uniform_splits && batch <= 64;
   if (compact) {
-    const bool captured = is_capturing(st);
-    int units = 0;
-    const auto list = [&](int b, int i) {
-      compact = compact && units < kMaxUnits;
-      if (compact) a.unit[units >> 1] |= (uint32_t)(b | i << 6) << (16 * (units & 1));
-      ++units;
-    };
     int used[64];
-    for (int b = 0; b < batch && compact; ++b) {
+    int64_t units = 0;
+    for (int b = 0; b < batch; ++b) {
       const int N = std::min(host_n_nodes[b], n_max);
       const int64_t T = (int64_t)host_ctx_len[b] + N;
       // A sequence without nodes has one unit, which reports its status.
       used[b] = N > 0 ? (int)((T + p.tps - 1) / p.tps) : 1;
-      for (int i = 0; i < used[b] && compact; ++i) list(b, i);
-      a.seq_splits[b] = captured ? p.max_splits : used[b];
+      units += used[b];
     }
-    for (int b = 0; b < batch && captured; ++b)
-      for (int i = used[b]; i < p.max_splits && compact; ++i) list(b, i);
-    a.row_blocks = p.row_blocks;
+    const int64_t blocks = (int64_t)hkv * p.row_blocks, wgs = units * blocks, all = blocks * p.max_splits * batch;
+    const int64_t cus = device_cu_count();
+    const bool small = path == Path::kBf16 && p.rows_per_wg <= 64 && p.tps <= kMinTps;
+    compact = all > (small ? p.wgs_per_cu : 1) * cus && (wgs <= cus || all > p.wgs_per_cu * cus);
+    const bool captured = compact && is_capturing(st);
+    if (captured) units = (int64_t)p.max_splits * batch;
     // The runtime takes fewer than 2^32 threads in a grid dimension.
-    compact = compact && (int64_t)units * hkv * p.row_blocks * 64 * p.nw < (int64_t(1) << 32);
-    if (compact) grid = dim3((unsigned)(units * hkv * p.row_blocks));
+    compact = compact && units <= kMaxUnits && units * blocks * 64 * p.nw < (int64_t(1) << 32);
+    if (compact) {
+      int u = 0;
+      const auto list = [&](int b, int i) {
+        a.unit[u >> 1] |= (uint32_t)(b | i << 6) << (16 * (u & 1));
+        ++u;
+      };
+      for (int b = 0; b < batch; ++b) {
+        for (int i = 0; i < used[b]; ++i) list(b, i);
+        a.seq_splits[b] = captured ? p.max_splits : used[b];
+      }
+      for (int b = 0; b < batch && captured; ++b)
+        for (int i = used[b]; i < p.max_splits; ++i) list(b, i);
+      a.row_blocks = p.row_blocks;
+      grid = dim3((unsigned)(units * blocks));
+    }
   }
   const Args& full = a;
 #define CURE_ATTN(threads, kernel, ...)                                                                    \

@@ -1,7 +1,8 @@
-"""GPU parity of ragged attention launches, which hold only the workgroups with work.
+"""GPU parity of ragged attention launches, which may hold only the workgroups with work.
 
 The host lists each sequence's splits in the kernel arguments (up to 64 sequences
-and 512 splits in all); other launches are a grid over sequences and splits. Both
+and 512 splits in all, where a grid over sequences and splits would not fit the GPU
+at one workgroup per CU); other launches are that grid. Both
 forms against the float64 oracle: at the limits of the list, with sequences
 without nodes or context, with forced split counts, for every kernel family, and
 with host sizes that are not the device's (they only plan the launch, so any
@@ -30,13 +31,20 @@ def check(w, dev, ref, **kw):
     ("bf16", 2, 4, 128, [16, 9, 0, 16, 3]), ("bf16", 1, 4, 128, [48, 40, 48, 0, 33]),
     ("bf16", 1, 4, 128, [80, 80, 65, 10, 0]), ("bf16", 2, 4, 128, [120, 4, 0, 100, 77]),
     ("bf16", 3, 2, 64, [20, 0, 7, 20, 20]), ("bf16", 1, 4, 64, [48, 30, 48, 0, 11]),
+    ("bf16", 1, 4, 64, [60, 49, 60, 0, 11]),
     ("f32", 2, 4, 64, [12, 0, 12, 5, 1]), ("f32", 1, 1, 128, [9, 16, 2, 0, 16])])
 @pytest.mark.parametrize("kv_split", [0, 5])
-def test_every_kernel_family(dtype, hkv, group, d, nodes, kv_split):
-    say("ragged", dtype, hkv, group, d, nodes, kv_split)
-    ctx = [700, 0, 300, 1500, 65]
+@pytest.mark.parametrize("heads", ["few", "many"])
+def test_every_kernel_family(dtype, hkv, group, d, nodes, kv_split, heads):
+    say("ragged", dtype, hkv, group, d, nodes, kv_split, heads)
+    ctx, sample = [700, 0, 300, 1500, 65], None
+    if heads == "many":                       # five splits or more of five sequences, 14 heads: listed
+        hkv, sample = 14, [(b, i) for b in range(5) for i in sorted({0, nodes[b] // 2, nodes[b] - 1}) if 0 <= i < nodes[b]]
     w = general_tree_workload(21, 5, hkv, group, d, nodes, ctx, "nested", dtype=dtype)
-    check(w, upload(w), oracle_attn(w), kv_split=kv_split)
+    o, lse, st = gpu_attn(w, upload(w), kv_split=kv_split)
+    torch.cuda.synchronize()
+    assert st.tolist() == [pc.CURE_OK] * 5
+    check_attn(w, o, lse, *oracle_attn(w, sample=sample), sample=sample)
 
 
 @pytest.mark.parametrize("batch", [63, 64, 65])
@@ -46,7 +54,7 @@ def test_batches_around_the_list_of_sequences(batch, dtype):
     ctx = [int(c) for c in rng.integers(0, 900, batch)]
     nodes = [int(n) for n in rng.integers(0, 9, batch)]
     nodes[-1], ctx[-1] = 8, 899
-    w = general_tree_workload(22, batch, 1, 4, 64, nodes, ctx, "uniform", dtype=dtype)
+    w = general_tree_workload(22, batch, 3, 4, 64, nodes, ctx, "uniform", dtype=dtype)
     check(w, upload(w), oracle_attn(w))
 
 
@@ -64,9 +72,10 @@ def test_splits_around_the_list(last, listed, dtype):
 
 @pytest.mark.parametrize("dtype,group", [("bf16", 4), ("f32", 2)])
 @pytest.mark.parametrize("host", ["larger", "smaller", "swapped", "none_here"])
-def test_host_sizes_only_plan(dtype, group, host):
+@pytest.mark.parametrize("hkv", [2, 24])               # a full grid, and listed (but for "smaller")
+def test_host_sizes_only_plan(dtype, group, host, hkv):
     ctx, nodes = [700, 300, 1500, 65], [16, 12, 16, 5]
-    w = general_tree_workload(24, 4, 2, group, 128, nodes, ctx, "forest", dtype=dtype)
+    w = general_tree_workload(24, 4, hkv, group, 128, nodes, ctx, "forest", dtype=dtype)
     dev, ref = upload(w), oracle_attn(w)
     hc, hn = {"larger": ([2000, 900, 1600, 900], [16] * 4), "smaller": ([300, 20, 700, 0], [3, 1, 16, 5]),
               "swapped": (ctx[::-1], nodes[::-1]), "none_here": ([700, 300, 1500, 65], [0, 12, 16, 0])}[host]
@@ -101,9 +110,10 @@ def test_merges_of_many_rows(d, hkv, group, kv_split, ragged):
 
 @pytest.mark.parametrize("dtype,group,d", [("bf16", 4, 128), ("bf16", 12, 64), ("f32", 2, 128)])
 @pytest.mark.parametrize("host", ["swapped", "shorter"])
-def test_a_captured_launch_replays_with_other_lengths(dtype, group, d, host):
+@pytest.mark.parametrize("hkv", [2, 12])               # a full grid, and listed
+def test_a_captured_launch_replays_with_other_lengths(dtype, group, d, host, hkv):
     ctx, nodes = [1500, 300, 2600, 65], [16, 12, 16, 5]
-    w = general_tree_workload(26, 4, 2, group, d, nodes, ctx, "forest", dtype=dtype)
+    w = general_tree_workload(26, 4, hkv, group, d, nodes, ctx, "forest", dtype=dtype)
     dev, ref = upload(w), oracle_attn(w)
     hc, hn = (ctx[::-1], nodes[::-1]) if host == "swapped" else ([40, 0, 1900, 65], [1, 0, 16, 5])
     call = lambda: pc.cure_tree_attn(dev["q"], dev["k"], dev["v"], dev["kv_off"], dev["ctx_len"], dev["n_nodes"],

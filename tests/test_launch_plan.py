@@ -57,9 +57,9 @@ def is_compact(launch):
     return "CompactArgs" in launch[0]
 
 
-# Eight sequences of 100 to 4000 tokens and 16 nodes, 8 kv-heads: forced splits of 512 tokens.
-RAGGED = dict(ctx=[4000, 100, 900, 1500, 2000, 300, 3000, 600], nodes=[16] * 8, hq=32, hkv=8, d=128, kv_split=8)
-SPLITS = [-(-(c + 16) // 512) for c in RAGGED["ctx"]]
+# Eight sequences of 100 to 4000 tokens and 32 nodes, 8 kv-heads: forced splits of 512 tokens.
+RAGGED = dict(ctx=[4000, 100, 900, 1500, 2000, 300, 3000, 600], nodes=[32] * 8, hq=32, hkv=8, d=128, kv_split=8)
+SPLITS = [-(-(c + 32) // 512) for c in RAGGED["ctx"]]
 
 
 def test_a_captured_ragged_launch_has_room_for_other_lengths(launches):
@@ -70,21 +70,10 @@ def test_a_captured_ragged_launch_has_room_for_other_lengths(launches):
     assert is_compact(eager[0]) and eager[0][1] == (sum(SPLITS) * 8, 1, 1)
     assert is_compact(captured[0]) and captured[0][1] == (8 * 8 * 8, 1, 1)
     # More than the table holds: the grid over sequences and splits.
-    many = dict(RAGGED, ctx=RAGGED["ctx"] * 3, nodes=[16] * 24, kv_split=32)
+    many = dict(RAGGED, ctx=RAGGED["ctx"] * 3, nodes=[32] * 24, kv_split=32)
     eager, captured = launches(many, dict(many, capturing=True))
     assert is_compact(eager[0])
     assert not is_compact(captured[0]) and captured[0][1] == (8, 32, 24)
-
-
-def test_the_list_holds_512_splits(launches):
-    """Sequences of 200, 150, 100 and 61 to 63 splits of 64 tokens: listed up to 512 in all, a grid over
-    sequences and splits beyond."""
-    call = lambda last: dict(ctx=[64 * s - 36 for s in (200, 150, 100, last)], nodes=[6] * 4, hq=2, hkv=1, d=64,
-                             kv_split=200)
-    below, at, above = [got[0] for got in launches(call(61), call(62), call(63))]
-    assert is_compact(below) and below[1] == (511, 1, 1)
-    assert is_compact(at) and at[1] == (512, 1, 1)
-    assert not is_compact(above) and above[1] == (1, 200, 4)
 
 
 def test_the_list_holds_512_splits(launches):
@@ -132,3 +121,18 @@ def test_wide_trees_at_head_dim_64_keep_the_splits_of_two_workgroups_per_cu(laun
         wide = -(-4 * nodes // -(-4 * nodes // 256)) > 192         # blocks of more than 192 rows, balanced
         small = batch * splits * hkv * -(-4 * nodes // 192) <= 256
         assert ("tree_attn_mfma" in name) == (wide and not small), (name, batch, tokens, nodes)
+
+
+def test_ragged_launches_that_fit_are_not_listed(launches):
+    """Where the CUs hold the full grid at one workgroup each there is nothing to gain from a list, nor at two
+    each when the workgroups with work need that too."""
+    call = lambda ctx, nodes, hkv, d: dict(ctx=ctx, nodes=[nodes] * len(ctx), hq=4 * hkv, hkv=hkv, d=d)
+    one, half, two, more = [got[0] for got in launches(
+        call([1708, 2854], 6, 8, 64),                      # 8 heads x 12 splits x 2
+        call([2600, 900, 1000], 32, 8, 128),               # 8 x 11 x 3, of which 160 have work
+        call([854, 1781, 1300, 1500], 100, 8, 64),         # two blocks of 8 heads x 8 x 4, 400
+        call([854, 1781, 1300, 1500] * 2, 100, 8, 64))]    # twice as many
+    assert not is_compact(one) and one[1] == (8, 12, 2)
+    assert is_compact(half) and half[1] == (8 * (11 + 4 + 5), 1, 1)
+    assert not is_compact(two) and two[1][0] * two[1][1] * two[1][2] <= 512
+    assert is_compact(more)
