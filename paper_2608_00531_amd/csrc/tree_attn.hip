@@ -2079,15 +2079,19 @@ Plan make_plan(int32_t batch, int32_t hq, int32_t hkv, int32_t d, int32_t n_max,
     return z * kTile;
   };
   int64_t tps;
-  // fp32 blocks that overfill the chip in single splits may leave most of a
-  // last round idle (640 blocks of 512 slots: 62 % used). Then the bf16 plan's
-  // splits are taken, which spread that round thinner (8 sequences of 8k tokens,
-  // 80 nodes: 948 -> 802 us); the workspace covers them. At head dim 64 a CU
-  // holds three of these workgroups, so the round is not idle (16 sequences of
-  // 500 tokens, 768 blocks: 41 us in single splits, 64 split).
+  // fp32 blocks that overfill the chip in single splits may leave much of a last round
+  // idle (640 blocks of 512 slots: 62 % used). Then the bf16 plan's splits are taken, which
+  // spread that round thinner; the workspace covers them. Single splits and these, us a
+  // call at 80 nodes: 8 sequences of 8k tokens 935 and 815, 10 of 4k (78 % used) 626 and
+  // 559, 9 of 0.7k - 4k (70 %) 407 and 354, 8 of 0.4k - 1.4k 181 and 161, though 9 of 2.5k
+  // 320 and 335. At 0.7k - 1.2k tokens the merge costs what the round gains (8 of 700 119
+  // and 145, 9 of 1.2k 181 and 197), and 88 % used and more leave nothing to gain (11 of 700
+  // 146 and 153 in two splits). At head dim 64 a CU holds three of these workgroups, so the
+  // round is not idle (16 sequences of 500 tokens, 768 blocks: 41 in single splits, 64 split).
   const auto fp32_tail_idle = [&]() {
     const int64_t wgs = workgroups(round_tile(t_max));
-    return path == Path::kF32 && d == 128 && wgs > slots && 5 * wgs < 4 * ((wgs + slots - 1) / slots * slots);
+    return path == Path::kF32 && d == 128 && t_max > 1280 && wgs > slots &&
+           5 * wgs < 4 * ((wgs + slots - 1) / slots * slots);
   };
   if (kv_split > 0) {
     tps = round_tile((t_max + kv_split - 1) / kv_split);

@@ -1,8 +1,9 @@
 """GPU parity of the fp32 matrix-core attention kernel at the edges of its dispatch.
 
-The kernel deals a workgroup's four waves over 64 query rows, or over 32 or 16
-rows and the tile's tokens when a kv-head has no more rows, and takes operands
-that are 16-byte aligned; everything else in fp32 stays on the vector-ALU kernel.
+The kernel works on blocks of 32 query rows (16 when a kv-head has no more), its four
+waves over the block's 16-row groups and two or four shares of each tile's tokens, and
+takes operands that are 16-byte aligned; everything else in fp32 stays on the
+vector-ALU kernel.
 Outputs against the float64 oracle at the fp32 bars of the other fp32 tests
 (1e-5 output, 1e-4 log-sum-exp: sums of a few hundred fp32 terms of N(0, 1)
 inputs, each rounded at 2^-24).
@@ -23,7 +24,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("hkv,group,nodes", [
     (2, 1, [1, 3]), (2, 1, [16, 9]), (1, 4, [4, 2]),       # up to 16 rows: tokens over 4 waves
     (2, 1, [17, 32]), (3, 2, [16, 5]),                     # up to 32 rows: tokens over 2 waves
-    (2, 1, [33, 8]), (2, 4, [16, 15]), (1, 8, [9, 80])])   # rows over 4 waves, row blocks
+    (2, 1, [33, 8]), (2, 4, [16, 15]), (1, 8, [9, 80])])   # row blocks of 32
 @pytest.mark.parametrize("ctx,kv_split", [([0, 31], 0), ([63, 130], 0), ([500, 1], 3), ([257, 640], 0)])
 def test_row_and_token_shares(d, hkv, group, nodes, ctx, kv_split):
     say("f32", d, hkv, group, nodes, ctx, kv_split)
@@ -32,6 +33,23 @@ def test_row_and_token_shares(d, hkv, group, nodes, ctx, kv_split):
     torch.cuda.synchronize()
     assert st.tolist() == [pc.CURE_OK] * 2
     check_attn(w, o, lse, *oracle_attn(w))
+
+
+@pytest.mark.parametrize("nodes,ctx", [
+    ([80] * 8, [1400] * 8), ([80, 80, 31, 80, 80, 0, 80, 64], [1400, 400, 650, 100, 1300, 0, 1000, 300])])
+def test_splits_of_launches_that_overfill_the_chip(nodes, ctx):
+    """640 blocks of 32 rows, as single splits 62 % of the two rounds that they take on 256 CUs, run in
+    shorter splits instead."""
+    say("f32 tail", nodes, ctx)
+    slots = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    blocks = 8 * 8 * (80 * 4 // 32)
+    assert blocks > slots and 5 * blocks < 4 * (-(-blocks // slots) * slots)
+    w = general_tree_workload(10, 8, 8, 4, 128, nodes, ctx, "nested", dtype="f32")
+    sample = [(b, i) for b in range(8) for i in sorted({0, nodes[b] // 2, nodes[b] - 1}) if 0 <= i < nodes[b]]
+    o, lse, st = gpu_attn(w, upload(w))
+    torch.cuda.synchronize()
+    assert st.tolist() == [pc.CURE_OK] * 8
+    check_attn(w, o, lse, *oracle_attn(w, sample=sample), sample=sample)
 
 
 @pytest.mark.parametrize("scale", [-0.125, 0.0])

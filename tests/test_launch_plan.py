@@ -123,6 +123,21 @@ def test_wide_trees_at_head_dim_64_keep_the_splits_of_two_workgroups_per_cu(laun
         assert ("tree_attn_mfma" in name) == (wide and not small), (name, batch, tokens, nodes)
 
 
+def test_fp32_launches_that_leave_the_last_round_idle_are_split(launches):
+    """80 nodes on 8 kv-heads of four heads are ten 32-row blocks a kv-head: 640 blocks for eight
+    sequences, of which 128 would fill a quarter of a second round of 512. They take splits; five
+    sequences (400 blocks), sixteen (1280, 83 % of three rounds) and short ones do not."""
+    call = lambda batch, tokens=1500, **kw: dict(dict(ctx=[tokens - 80] * batch, nodes=[80] * batch, hq=32, hkv=8,
+                                                      d=128, dtype="f32"), **kw)
+    eight, ragged, five, sixteen, short = [got[0] for got in launches(
+        call(8), call(8, ctx=[1400, 400, 650, 100, 1300, 0, 1000, 300]), call(5), call(16), call(8, 1280))]
+    assert eight[1] == (80, 4, 8)                   # 384-token splits
+    assert is_compact(ragged) and ragged[1][0] > 640
+    assert five[1] == (80, 1, 5)
+    assert sixteen[1] == (80, 1, 16)
+    assert short[1] == (80, 1, 8)
+
+
 def test_ragged_launches_that_fit_are_not_listed(launches):
     """Where the CUs hold the full grid at one workgroup each there is nothing to gain from a list, nor at two
     each when the workgroups with work need that too."""
