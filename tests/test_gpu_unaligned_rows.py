@@ -2,7 +2,8 @@
 
 A row length or a base address that is no multiple of 16 bytes puts each row's
 first 16-byte boundary at another entry. The vectors start there; the entries
-before and after them are taken singly. Every base offset of a 16-byte window,
+before and after them are taken singly, as are all of a margin pass's rows of fewer
+than 1280 entries. Every base offset of a 16-byte window,
 vocabularies around the vector, chunk and loop-step sizes, with the best
 entries in the first and last positions of the row and at the chunk edges,
 against the oracle: indices bit-exact.
@@ -32,7 +33,7 @@ def shifted(a, dtype, off):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("vocab", [2, 5, 9, 17, 8191, 8200, 16385, 50257, 70001])
+@pytest.mark.parametrize("vocab", [2, 5, 9, 17, 1279, 1280, 1289, 8191, 8200, 16385, 50257, 70001])
 def test_margins_on_rows_that_start_anywhere(dtype, vocab):
     rng = np.random.default_rng(vocab)
     rows = 24

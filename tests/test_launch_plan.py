@@ -1,4 +1,4 @@
-"""Which kernels a tree-attention call launches, and with how many workgroups, on the CPU.
+"""Which kernels a call launches, and with how many workgroups, on the CPU.
 
 A stub of the HIP runtime (launch_stub.cpp) records the launches of the built library in a
 process of its own; nothing runs on a GPU.
@@ -23,7 +23,14 @@ lib = c.CDLL(sys.argv[2])
 p, i, f, z = c.c_void_p, c.c_int32, c.c_float, c.c_size_t
 attn = lib.cure_tree_attn
 attn.argtypes = [p] * 5 + [i] * 6 + [f] + [p] * 4 + [i, p, p, i, c.c_uint32, p, p, z, p]
-def call(ctx, nodes, hq, hkv, d, dtype="bf16", kv_split=0, capturing=False):
+lib.cure_margins.argtypes = [p, i, i, i, i, c.c_int64] + [p] * 6 + [i, f, i, i, p, p, p, z, p]
+def margins(vocab, ld, offset, dtype):
+    stub.stub_reset(0)
+    t = 4096
+    status = lib.cure_margins(t + offset, 0 if dtype == "f32" else 1, 1, 4, vocab, ld, t, t, t, t, t, t, 0, 1.0, 0, 1,
+                              None, None, t, 1 << 60, None)
+    return status, [l.split() for l in stub.stub_launches().decode().splitlines()]
+def attention(ctx, nodes, hq, hkv, d, dtype="bf16", kv_split=0, capturing=False):
     array = lambda v: (i * len(v))(*v)
     t, b = 4096, len(ctx)
     stub.stub_reset(int(capturing))
@@ -31,7 +38,7 @@ def call(ctx, nodes, hq, hkv, d, dtype="bf16", kv_split=0, capturing=False):
     status = attn(t, t, t, t, t, code, code, b, hq, hkv, d, 0.125, t, t, t, t, max(nodes), array(ctx),
                   array(nodes), kv_split, 0, t, t, 1 << 60, None)
     return status, [l.split() for l in stub.stub_launches().decode().splitlines()]
-print(json.dumps([call(**kw) for kw in json.loads(sys.argv[3])]))
+print(json.dumps([(margins if "vocab" in kw else attention)(**kw) for kw in json.loads(sys.argv[3])]))
 """
 
 
@@ -151,3 +158,12 @@ def test_ragged_launches_that_fit_are_not_listed(launches):
     assert is_compact(half) and half[1] == (8 * (11 + 4 + 5), 1, 1)
     assert not is_compact(two) and two[1][0] * two[1][1] * two[1][2] <= 512
     assert is_compact(more)
+
+
+@pytest.mark.parametrize("dtype,size", [("bf16", 2), ("f32", 4)])
+def test_short_logits_rows_between_vector_boundaries_are_read_singly(launches, dtype, size):
+    """Rows that all start at a 16-byte boundary take vectors whatever their length, others from 1280 entries."""
+    vectors = lambda *rows: ["Lb1" in got[0][0].split("margins_kernel")[1][:10] for got in launches(
+        *[dict(vocab=v, ld=ld, offset=off, dtype=dtype) for v, ld, off in rows])]
+    assert vectors((1003, 1008, 0), (1003, 1003, 0), (1008, 1008, size), (1279, 1279, 0), (1281, 1281, 0),
+                   (1280, 1280, size)) == [True, False, False, False, True, True]
