@@ -22,7 +22,7 @@
 //  * tree_attn_mfma: the same with 32x32x16 MFMAs and 32 rows per wave, for head dim 64
 //    beyond 192 rows, in blocks of up to 256.
 //  * tree_attn_f32: fp32 on the fp32 matrix instructions, the same scheme with
-//    the rows or the tokens of a block dealt over four waves.
+//    the rows and the tokens of a block dealt over four waves.
 //  * tree_attn_valu: fp32 or bf16, any supported shape, scale and alignment;
 //    plain vector ALU code.
 // A split writes normalised partial O and its log-sum-exp; attn_merge combines
@@ -358,7 +358,8 @@ __global__ __launch_bounds__(256) void tree_attn_valu(Args a) {
 // offset past the resource, which touch no memory. LDS rows are 16-byte-chunk
 // XOR-swizzled so that both the K reads (one row per lane) and the transposed V
 // reads (4 rows x 16 columns per 16 lanes, ds_read_b64_tr_b16) spread over the
-// banks. The DMA is issued from inline assembly on purpose: written through the
+// banks: without conflicts at head dim 128, with 2.3 conflict cycles per LDS
+// instruction counted at 64. The DMA is issued from inline assembly on purpose: written through the
 // compiler builtin, every later LDS read of the current tile gets a wait on the
 // next tile's DMA (the compiler cannot tell the buffers apart), which serialises
 // the pipeline. Ordering is explicit instead: each loop iteration starts with
@@ -758,9 +759,9 @@ __global__ __launch_bounds__(64 * NW, NBUF > 2 ? 1 : 2) void tree_attn_mfma(A a)
 // MFMA split kernel with 16 query rows per wave (v_mfma_f32_16x16x32_bf16).
 //
 // A tile's row maxima are reduced only when a rescale could be due. Few registers
-// per wave, so that two 8-wave
-// workgroups (four waves per SIMD) share a CU, and row blocks of up to 256
-// rows fit one 16-wave workgroup with the rows spread evenly over the SIMDs.
+// per wave, so that two 8-wave workgroups (four waves per SIMD) share a CU, and row
+// blocks of up to 256 rows fit one 16-wave workgroup with the rows spread evenly over
+// the SIMDs.
 // Wider trees take several row blocks of equal size (a multiple of 16 rows).
 // The row blocks of one kv-head and split are hkv workgroup ids apart: with
 // hkv a multiple of 8 the dispatcher, which deals workgroups to the 8 XCDs in
@@ -1449,7 +1450,10 @@ void tree_attn_rg(A a) {
 // and sums: the same precision as the vector-ALU kernel).
 //
 // Bound by the fp32 matrix rate (256 flop per clock and CU; a large fp32 GEMM
-// reaches 137 TFLOP/s on this card). A workgroup is four waves over a block of
+// reaches 137 TFLOP/s on this card) and by what the matrix unit waits for: on the
+// first batch below it is busy for 64 % of the cycles in which a SIMD holds its two
+// waves, these wait for 22 % of theirs, and an LDS instruction has 1.7 conflict
+// cycles. A workgroup is four waves over a block of
 // 32 rows (or 16, when a kv-head has no more), each wave owning 16 query rows
 // and 1 / WT of every tile's tokens (WT = 2 or 4), so no wave idles; the token
 // shares are combined through LDS at the end. Small blocks fill two workgroups
@@ -1473,8 +1477,9 @@ void tree_attn_rg(A a) {
 //     stands for column 64 h + 4 c' + i, so that one 16-byte read of V (row
 //     4 g + r, columns 64 h + 4 c .. +3) feeds four MFMAs
 //     D register r of block 4 h + i = O column 64 h + 16 g + 4 r + i of row c
-// LDS rows are XOR-swizzled by 16-byte chunk: the K reads (16 rows, one chunk
-// column) and the V reads (one row, 16 chunks) both cover all banks evenly.
+// LDS rows are XOR-swizzled by 16-byte chunk, so that the 16 lanes of a group cover
+// all banks in the K reads (16 rows, one chunk column) and in the V reads (one row,
+// 16 chunks).
 // Hidden and out-of-range scores are replaced, not added to: an infinite or NaN
 // K row that a node does not see leaves its result alone.
 template <int D, int WT>
@@ -1874,9 +1879,10 @@ __global__ __launch_bounds__(256) void attn_merge(A a) {
 // Bound by the partials' round trips, so by how many waves of them there are: a
 // wave per row takes several rounds once a launch has more rows than the chip
 // holds waves (8192), which is what large launches with few splits have. Per
-// call, wave per row and here: ragged batch (3 splits, 24.6k rows) 59.8 and
-// 57.9 us, 80-node trees of 8 sequences (4 splits, 20.5k rows) 102.5 and 101.1,
-// head dim 64 (2 splits, 24.6k rows) 33.3 and 32.3, (16.4k rows) 35.8 and 35.1.
+// call, wave per row and here: ragged batch (3 splits, 24.6k rows) 61.2 and
+// 58.8 us; 80-node trees of 8 sequences (4 splits, 20.5k rows) 105.9 and 103.2,
+// where the runs of one side differ by 2.8 %; head dim 64 (2 splits, 24.6k rows)
+// 33.3 and 32.3, (16.4k rows) 35.8 and 35.1.
 // With fewer rows or more splits the wave per row is ahead, as it spreads a row's
 // loads over more lanes: fp32 (8.2k rows) 46.4 and 47.1, 2 sequences (2k rows)
 // 11.3 and 12.7; 32k context (8 splits) 105.5 and 106.8, head dim 64 (11

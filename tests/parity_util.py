@@ -25,7 +25,7 @@ ATTN_TOL = {"f32": 1e-5, "bf16": 2e-2}
 # unit roundoff of bf16's 8-bit significand, so the sum's relative error is at
 # most 2^-8 and the log-sum-exp is off by at most ln(1 + 2^-8) = 3.9e-3, which
 # a node that sees only a few keys (one of them dominant) reaches. fp32: the
-# vector-ALU kernel sums ~10^3 fp32 terms, relative error ~ L * 2^-24.
+# kernels sum ~10^3 fp32 terms, relative error ~ L * 2^-24.
 LSE_TOL = {"f32": 1e-4, "bf16": 4e-3}
 
 
